@@ -251,7 +251,10 @@ int lbm_set_gw(lbm_ctx *c, const double *gw_host);
  *   1      two passes (psi pass, then the force-collide-stream pass reading psi through LDS);
  *   2      (default) two time steps per launch (the first step's populations stay in LDS;
  *          72 bytes per lattice update), an odd remainder step runs fused; output tile 64x8,
- *          or the wide 32x4 workgroups (schedule 39) on lattices of at most 384 such tiles;
+ *          or the wide 32x4 workgroups (schedule 39) on lattices of at most 384 such tiles.
+ *          Lattices without a solid mask that fill the GPU (from about a million nodes) take three
+ *          steps per launch instead, by strips that march through registers (48 bytes per lattice
+ *          update), unless an output tile was chosen (32+t);
  *   16+t   fused with tile shape t (0..7: 64x4, 64x8, 64x16, 128x4, and the overlapped
  *          62-column tiles with 4, 6, 8, 14 rows);
  *   32+t   two steps per launch with output tile t (0..5: 64x8, 64x4, 128x4, 64x16, 32x8,
@@ -296,7 +299,7 @@ int lbm_backward(lbm_ctx *c, int64_t nsteps, int32_t K, void *d_ws, size_t bytes
 /*
  * `count` independent instances (each with its own lbm_params: lattice size, wall force, G_w,
  * viscosities ...) advanced together. All instances' tiles form one work-list, executed by one
- * launch per time step (schedule 0) or per two steps (schedule 2), replayed from captured
+ * launch per time step (schedule 0) or per two or three steps (schedule 2), replayed from captured
  * hipGraphs, or by one persistent launch for n steps (schedule 1: an occupancy-sized grid whose
  * workgroups take tiles from a ticket counter per XCD and advance them two steps at a time, with
  * a grid barrier between the two-step passes, and a per-step launch for an odd last step;
@@ -317,7 +320,8 @@ typedef struct {
     int32_t reserved;     /* must be 0 */
     int32_t waves_per_cu; /* persistent schedule: workgroups per compute unit (0 = occupancy) */
     int32_t schedule;     /* 0 per-step launches, 1 persistent, 2 two steps per launch (output
-                             tiles of the tile shape) */
+                             tiles of the tile shape; without solid masks three, by marching
+                             strips, where the ensemble fills the GPU) */
 } lbm_tune;
 
 typedef struct lbm_batch lbm_batch;

@@ -34,6 +34,7 @@ struct lbm_ctx {
     int schedule;
     int tile;
     int tile2;  // output tile of the two-step kernel
+    int march;  // rows per segment of the marching strips, which schedule 2 then uses; 0: tiles
     // last lbm_forward_ckpt: where it started, its length and checkpoint interval
     int64_t adj_start, adj_nsteps;
     int32_t adj_K;
@@ -573,6 +574,8 @@ static int create_impl(const lbm_params* p, const uint8_t* solid, const double* 
     // per two-step launch (one MI355X; 64x8 / 64x4 / wide 32x4): 128x64 7.24 / 6.54 / 5.55 us,
     // 256x128 7.35 / 6.74 / 5.78, 384x192 7.76 / 8.58 / 7.98, 512x256 8.39 / 9.44 / 10.56.
     c->tile2 = ((p->nx + 31) / 32) * ((y_hi_of(p) - y_lo_of(p) + 4) / 4) <= 384 ? 7 : 0;
+    const lbm::MarchShape shape{p->nx, y_hi_of(p) - y_lo_of(p) + 1};
+    c->march = solid ? 0 : lbm::march_rows(&shape, 1);
     c->adj_start = -1;
     c->adj_nsteps = 0;
     c->adj_K = 0;
@@ -670,6 +673,7 @@ int lbm_set_schedule(lbm_ctx* c, int32_t schedule) {
     if (schedule >= 32 && schedule < 40) {
         c->schedule = 2;
         c->tile2 = schedule - 32;
+        c->march = 0;
         return LBM_OK;
     }
     return fail(c, LBM_E_INVAL, "unknown schedule");
@@ -680,6 +684,15 @@ int lbm_set_schedule(lbm_ctx* c, int32_t schedule) {
 // swaps, single steps n).
 static hipError_t enqueue_steps(lbm_ctx* c, int64_t n, int cur, hipStream_t s, int* cur_out) {
     *cur_out = cur;
+    if (c->schedule == 2 && c->march) {
+        // a remainder of one step is left to two two-step launches
+        for (; n >= 3 && n != 4; n -= 3) {
+            hipError_t e = lbm::launch_march(c->kp, c->march, c->g[cur], c->g[cur ^ 1], c->gw, s);
+            if (e != hipSuccess) return e;
+            cur ^= 1;
+            *cur_out = cur;
+        }
+    }
     if (c->schedule == 2) {
         for (; n >= 2; n -= 2) {
             hipError_t e = lbm::launch_step2(c->kp, c->tile2, c->g[cur], c->g[cur ^ 1], c->gw, s);
@@ -1131,6 +1144,9 @@ struct lbm_batch {
     int* d_tile_inst;
     unsigned long long* d_bar;  // grid-barrier arrival counter of the persistent schedule
     int* d_flag;
+    lbm::MarchSeg* d_segs;  // work-list of the marching strips
+    int nsegs;              // 0: schedule 2 runs tiles
+    int visc;               // as in launch_batch_march
     std::vector<double*> psi, part, fin;
     int ntiles;
     int cur;
@@ -1142,7 +1158,7 @@ struct lbm_batch {
     int eos;   // lbm::EOS_CS or EOS_PW shared by every instance, else EOS_ANY
     std::vector<int32_t> rows;  // contact-line rows of the last record call (host copy)
     int* d_rows;
-    hipGraphExec_t graph[2];  // per-step schedule: kGraphChunk launches starting at parity 0 / 1
+    hipGraphExec_t graph[2];  // a chunk of steps (lbm_batch_step) starting at parity 0 / 1
     hipGraphExec_t pgraph;    // persistent schedule: reset + persistent kernel for pgraph_n steps
     int64_t pgraph_n;
     int pgraph_cur;
@@ -1172,7 +1188,8 @@ static int spin_limit_from_env() {
 }
 
 struct BatchLayout {
-    size_t off_desc, off_tiles, off_bar, off_rows, total;
+    size_t off_desc, off_tiles, off_bar, off_rows, off_segs, total;
+    std::vector<lbm::MarchSeg> segs;  // schedule 2 marches these strips (none: tiles)
     std::vector<size_t> off_inst;  // per instance: g0, g1, gw, psi, part, fin
     std::vector<Layout> L;
     int ntiles;
@@ -1203,6 +1220,15 @@ bool batch_layout(const lbm_params* p, int32_t count, int tile, BatchLayout* B) 
     o += align_up((size_t)lbm::kControlWords * 8, kAlign);
     B->off_rows = o;
     o += align_up((size_t)count * sizeof(int), kAlign);
+    B->off_segs = o;
+    if (!is_mask(&p[0])) {
+        std::vector<lbm::MarchShape> shapes(count);
+        for (int i = 0; i < count; ++i) shapes[i] = {p[i].nx, y_hi_of(&p[i]) - y_lo_of(&p[i]) + 1};
+        if (const int h = lbm::march_rows(shapes.data(), count))
+            for (int i = 0; i < count; ++i)
+                lbm::march_segments(shapes[i], i, y_lo_of(&p[i]), h, &B->segs);
+    }
+    o += align_up(B->segs.size() * sizeof(lbm::MarchSeg), kAlign);
     B->off_inst.resize(count);
     for (int i = 0; i < count; ++i) {
         B->off_inst[i] = o;
@@ -1283,6 +1309,8 @@ static int batch_create_impl(const lbm_params* p, int32_t count,
     for (int i = 0; i < count; ++i)
         if (p[i].walls == LBM_WALLS_WET_NODE) b->geo = lbm::GEO_WET;
     b->d_rows = (int*)(b->ws + B.off_rows);
+    b->d_segs = (lbm::MarchSeg*)(b->ws + B.off_segs);
+    b->nsegs = (int)B.segs.size();
     b->cur = 0;
     b->step = 0;
     b->tune = tn;
@@ -1352,7 +1380,13 @@ static int batch_create_impl(const lbm_params* p, int32_t count,
     if (e != hipSuccess) { delete b; return create_fail(LBM_E_HIP, "create: descriptor copy", e); }
     e = host_copy(s, b->d_tile_inst, tile_inst.data(), B.ntiles * sizeof(int),
                   hipMemcpyHostToDevice);
+    if (e == hipSuccess && b->nsegs)
+        e = host_copy(s, b->d_segs, B.segs.data(), B.segs.size() * sizeof(lbm::MarchSeg),
+                      hipMemcpyHostToDevice);
     if (e != hipSuccess) { delete b; return create_fail(LBM_E_HIP, "create: tile table copy", e); }
+    b->visc = b->kp[0].visc_const ? 1 : 2;
+    for (const KParams& k : b->kp)
+        if (k.visc_const != b->kp[0].visc_const) b->visc = 0;
     if ((e = hipStreamSynchronize(s)) != hipSuccess) { delete b; return create_fail(LBM_E_HIP, "create hipStreamSynchronize", e); }
     // persistent grid: co-resident workgroups only (occupancy x compute units)
     int dev = 0, cus = 0;
@@ -1389,22 +1423,33 @@ int lbm_batch_create_masked(const lbm_params* p, int32_t count, const uint8_t* c
                              out);
 }
 
-static int batch_direct(lbm_batch* b, int64_t n) {
-    if (b->tune.schedule == 2) {
-        for (; n >= 2; n -= 2) {
-            hipError_t e = lbm::launch_batch_step2(b->tune.tile, b->geo, b->eos, b->d_inst,
-                                                   b->d_tile_inst, b->ntiles, b->cur, b->stream);
-            if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, std::string("batch step: ") + hipGetErrorString(e));
-            b->cur ^= 1;
-            b->step += 2;
-        }
+// One launch of the ensemble's schedule from buffer parity `cur`, with n steps still to go;
+// *steps receives how many it makes. Schedule 2 makes three by marching strips where those are
+// the better choice (a remainder of one step is left to two two-step launches), else two.
+static hipError_t batch_launch(lbm_batch* b, int64_t n, int cur, int* steps) {
+    if (b->tune.schedule == 2 && b->nsegs && n >= 3 && n != 4) {
+        *steps = lbm::kMarchSteps;
+        return lbm::launch_batch_march(b->geo, b->eos, b->visc, b->d_inst, b->d_segs, b->nsegs, cur,
+                                       b->stream);
     }
-    for (int64_t i = 0; i < n; ++i) {
-        hipError_t e = lbm::launch_batch_step(b->tune.tile, b->geo, b->eos, b->d_inst, b->d_tile_inst,
-                                              b->ntiles, b->cur, b->stream);
+    if (b->tune.schedule == 2 && n >= 2) {
+        *steps = 2;
+        return lbm::launch_batch_step2(b->tune.tile, b->geo, b->eos, b->d_inst, b->d_tile_inst,
+                                       b->ntiles, cur, b->stream);
+    }
+    *steps = 1;
+    return lbm::launch_batch_step(b->tune.tile, b->geo, b->eos, b->d_inst, b->d_tile_inst,
+                                  b->ntiles, cur, b->stream);
+}
+
+static int batch_direct(lbm_batch* b, int64_t n) {
+    while (n > 0) {
+        int k = 0;
+        hipError_t e = batch_launch(b, n, b->cur, &k);
         if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, std::string("batch step: ") + hipGetErrorString(e));
         b->cur ^= 1;
-        b->step += 1;
+        b->step += k;
+        n -= k;
     }
     return LBM_OK;
 }
@@ -1470,31 +1515,28 @@ int lbm_batch_step(lbm_batch* b, int64_t n) {
         b->step += n;
         return LBM_OK;
     }
-    // per-step schedule: replay a graph of kGraphChunk launches, then the remainder directly
-    int64_t chunks = n / kGraphChunk;
+    // replay a graph of kGraphChunk steps, then launch the remainder directly (60 steps where a
+    // launch makes three: either way an even number of launches)
+    const int chunk = b->tune.schedule == 2 && b->nsegs ? 60 : kGraphChunk;
+    int64_t chunks = n / chunk;
     for (int64_t k = 0; k < chunks; ++k) {
         const int cur = b->cur;
         if (!b->graph[cur]) {
             int rc = capture(b, &b->graph[cur], [&]() {
-                const bool two = b->tune.schedule == 2;  // two steps per launch
-                for (int i = 0; i < (two ? kGraphChunk / 2 : kGraphChunk); ++i) {
-                    hipError_t e = two ? lbm::launch_batch_step2(b->tune.tile, b->geo, b->eos, b->d_inst,
-                                                                 b->d_tile_inst, b->ntiles,
-                                                                 (cur + i) & 1, b->stream)
-                                       : lbm::launch_batch_step(b->tune.tile, b->geo, b->eos, b->d_inst,
-                                                                b->d_tile_inst, b->ntiles,
-                                                                (cur + i) & 1, b->stream);
-                    if (e != hipSuccess) return e;
+                hipError_t e = hipSuccess;
+                for (int left = chunk, c = cur, m = 0; left > 0 && e == hipSuccess; left -= m) {
+                    e = batch_launch(b, left, c, &m);
+                    c ^= 1;
                 }
-                return hipSuccess;
+                return e;
             });
-            if (rc != LBM_OK) return batch_direct(b, n - k * kGraphChunk);  // no graph here
+            if (rc != LBM_OK) return batch_direct(b, n - k * chunk);  // no graph here
         }
         hipError_t e = hipGraphLaunch(b->graph[cur], b->stream);
         if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "graph launch");
-        b->step += kGraphChunk;  // an even number of buffer swaps: parity unchanged
+        b->step += chunk;  // an even number of buffer swaps: parity unchanged
     }
-    return batch_direct(b, n - chunks * kGraphChunk);
+    return batch_direct(b, n - chunks * chunk);
 }
 
 static int batch_check_abort(lbm_batch* b) {

@@ -16,6 +16,8 @@
 
 #include "lbm_device.h"
 #include "lbm_internal.h"
+#include "lbm_march.h"
+#include "lbm_wave.h"
 
 namespace lbm {
 
@@ -62,6 +64,21 @@ k_batch_step2(
     batch_tile_origin(D, t, TX, TY, x0, y0);
     step2_tile_any<TX, TY, GEO, EOS, false, false, NTH>(D->P, gptr(D->g[cur]), gptr(D->g[cur ^ 1]),
                                                         gptr(D->gw), x0, y0, lds);
+}
+
+// kMarchSteps steps per launch over the ensemble's list of segments, one per wave (march_strip).
+template <int GEO, int EOS, int VISC>
+__global__ __launch_bounds__(64 * kMarchWaves, 2) void k_batch_march(
+    const InstDesc* __restrict__ inst, const MarchSeg* __restrict__ segs, int n, int cur) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = xcd_tile(blockIdx.x, gridDim.x) * kMarchWaves + wave;
+    if (w >= n) return;
+    const MarchSeg S = segs[w];
+    const InstDesc* D = inst + S.inst;
+    const KParams P = D->P;
+    march_strip<kMarchSteps, GEO, EOS, VISC, DppLane>(P, gptr(D->g[cur]), gptr(D->g[cur ^ 1]),
+                                                      gptr(D->gw), S.x0, S.y0, S.y1,
+                                                      threadIdx.x & 63);
 }
 
 // Bounded wait (thread 0 of a workgroup) until *ctr >= target. Returns 0 when the run was
@@ -518,6 +535,26 @@ hipError_t launch_batch_adj_gw(const AdjInst* inst, int count, int max_nx, int k
     hipLaunchKernelGGL(k_batch_adj_gw, dim3((max_nx + 255) / 256, count), dim3(256), 0, s, inst,
                        k);
     return hipGetLastError();
+}
+
+hipError_t launch_batch_march(int geo, int eos, int visc, const InstDesc* inst,
+                              const MarchSeg* segs, int n, int cur, hipStream_t s) {
+    return dispatch(geo, eos, [&](auto g, auto e) {
+        constexpr int G = decltype(g)::value, E = decltype(e)::value;
+        if constexpr (G == GEO_MASK) {
+            return hipErrorInvalidValue;
+        } else {
+            auto go = [&](auto v) {
+                hipLaunchKernelGGL((k_batch_march<G, E, decltype(v)::value>),
+                                   dim3((n + kMarchWaves - 1) / kMarchWaves),
+                                   dim3(64 * kMarchWaves), 0, s, inst, segs, n, cur);
+                return hipGetLastError();
+            };
+            if (visc == 1) return go(std::integral_constant<int, 1>{});
+            if (visc == 2) return go(std::integral_constant<int, 2>{});
+            return go(std::integral_constant<int, 0>{});
+        }
+    });
 }
 
 hipError_t launch_batch_contact_line(const InstDesc* inst, const int* rows, int count, int cur,

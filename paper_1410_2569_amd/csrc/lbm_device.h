@@ -313,16 +313,14 @@ __device__ __forceinline__ void store_wall_force(const KParams& P, double* out, 
     if (y == P.ny - 2) { out[o + W] = Fx; out[pl + o + W] = Fy; }
 }
 
-// Forces, velocity and MRT collision of one node (Eqs. 2-4, 6, 7, 9 and 10/11/14):
-// in f[9] (pre-collision), rho, psi_c, cohesion sum (sx, sy), adhesion sum (Ax, Ay);
-// out f[9] overwritten with f* = M^-1 m*.
-__device__ __forceinline__ void collide(const KParams& P, double f[9], double rho, double psi_c,
-                                        double sx, double sy, double Ax, double Ay) {
+// Velocity and MRT collision of one node (Eqs. 2-4, 6 and 9) with its total force (Fx, Fy): in
+// f[9] (pre-collision), rho and the cohesion sum (sx, sy); out f[9] overwritten with f* = M^-1 m*.
+// VISC: the viscosity is the same in both phases (1), interpolated (2), or as P.visc_const says
+// (0).
+template <int VISC = 0>
+__device__ __forceinline__ void collide_force(const KParams& P, double f[9], double rho, double sx,
+                                              double sy, double Fx, double Fy) {
 #pragma clang fp contract(off)
-    // Eq. (7) cohesion plus the adhesion of Eq. (10)/(11)/(14)
-    double Fx, Fy;
-    total_force(P, rho, psi_c, sx, sy, Ax, Ay, Fx, Fy);
-
     // moments m = M f (rows rho, e, epsilon, jx, qx, jy, qy, pxx, pxy)
     const double ax = f[1] + f[3], ay = f[2] + f[4];
     const double sa = ax + ay;                       // axial sum
@@ -347,7 +345,7 @@ __device__ __forceinline__ void collide(const KParams& P, double f[9], double rh
 
     // shear relaxation rate from the phase-interpolated viscosity
     double snu;
-    if (P.visc_const) {
+    if (VISC == 1 || (VISC == 0 && P.visc_const)) {
         snu = P.s_nu_c;
     } else {
         double phi = (rho - P.rho_v) * P.inv_drho;
@@ -395,6 +393,27 @@ __device__ __forceinline__ void collide(const KParams& P, double f[9], double rh
     f[7] = bp - sp;
     f[6] = bm + sm;
     f[8] = bm - sm;
+}
+
+// Forces, velocity and MRT collision of one node (Eqs. 2-4, 6, 7, 9 and 10/11/14):
+// in f[9] (pre-collision), rho, psi_c, cohesion sum (sx, sy), adhesion sum (Ax, Ay);
+// out f[9] overwritten with f* = M^-1 m*.
+__device__ __forceinline__ void collide(const KParams& P, double f[9], double rho, double psi_c,
+                                        double sx, double sy, double Ax, double Ay) {
+    // Eq. (7) cohesion plus the adhesion of Eq. (10)/(11)/(14)
+    double Fx, Fy;
+    total_force(P, rho, psi_c, sx, sy, Ax, Ay, Fx, Fy);
+    collide_force(P, f, rho, sx, sy, Fx, Fy);
+}
+
+// collide() of a node without a solid neighbour (Ax = Ay = 0): the same bits without the adhesion
+// term, as fma(-pre, 0, z) is z.
+template <int VISC>
+__device__ __forceinline__ void collide_free(const KParams& P, double f[9], double rho,
+                                             double psi_c, double sx, double sy) {
+#pragma clang fp contract(off)
+    const double a = P.negG * psi_c;
+    collide_force<VISC>(P, f, rho, sx, sy, a * sx, a * sy);
 }
 
 // Macroscopic velocity of a node (Eq. 6) with the same force as collide().

@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <vector>
+
 #include "lbm_device.h"
 
 namespace lbm {
@@ -47,6 +49,25 @@ hipError_t launch_step(const KParams& P, int schedule, int tile, const double* g
 // gmid (optional, bounce-back or periodic rows): also receives the state after the first step
 hipError_t launch_step2(const KParams& P, int tile2, const double* gin, double* gout,
                         const double* gw, hipStream_t s, double* gmid = nullptr);
+// Marching strips (lbm_march.h): kMarchSteps steps per launch, in segments of h rows.
+constexpr int kMarchSteps = 3;
+constexpr int kSimds = 1024;  // 256 compute units of 4 SIMDs
+struct MarchShape {
+    int nx, rows;  // columns and fluid rows of a lattice
+};
+struct MarchSeg {
+    int inst, x0, y0, y1;  // a wave's lattice, first column and rows
+};
+// Rows per segment for these lattices advanced together (no solid masks), or 0 where the two-step
+// tiles are the better choice.
+int march_rows(const MarchShape* m, int count);
+// Appends the segments of one lattice.
+void march_segments(const MarchShape& m, int inst, int y_lo, int h, std::vector<MarchSeg>* out);
+hipError_t launch_march(const KParams& P, int h, const double* gin, double* gout, const double* gw,
+                        hipStream_t s);
+// visc: 1 every instance has one viscosity, 2 none has, 0 some have
+hipError_t launch_batch_march(int geo, int eos, int visc, const InstDesc* inst,
+                              const MarchSeg* segs, int n, int cur, hipStream_t s);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);  // bytes and p 8-byte aligned
 hipError_t launch_init(const KParams& P, const double* rho0, double* g, hipStream_t s);
 // droplets of the initial state (lbm_create_droplets): up to kMaxDroplets tanh profiles

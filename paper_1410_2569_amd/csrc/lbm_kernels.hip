@@ -9,6 +9,8 @@
 //   two-pass  psi pass (pull, rho, psi -> psi array with mirrored ghost rows), then the step
 //             kernel stages the psi tile plus halo in LDS: 72 + 8 B and 72 + 8 + 72 B per update.
 //   two-step  two time steps per launch with the intermediate state in LDS (step2_tile).
+//   marching  three time steps per launch on large lattices: strips of columns march through
+//             registers (march_strip).
 // With the wet-node wall scheme the boundary nodes also write their force (16 B) to the solid row,
 // which the next pull reads back; that traffic is confined to two rows of the lattice.
 #include <algorithm>
@@ -16,6 +18,8 @@
 
 #include "lbm_device.h"
 #include "lbm_internal.h"
+#include "lbm_march.h"
+#include "lbm_wave.h"
 
 namespace lbm {
 
@@ -97,6 +101,24 @@ __global__ __launch_bounds__(NTH, NTH == step2_threads(TX, TY, GEO)
     const int tile = xcd_tile(blockIdx.x, ntx * nty);
     step2_tile_any<TX, TY, GEO, EOS, MID, false, NTH>(P, gin, gout, gw, (tile % ntx) * TX,
                                                       P.y_lo + (tile / ntx) * TY, lds, gmid);
+}
+
+// kMarchSteps steps per launch: every wave marches one strip through one segment of h rows
+// (march_strip). Two waves per SIMD (256 registers each): three levels hold about 200.
+template <int GEO, int EOS, int VISC>
+__global__ __launch_bounds__(64 * kMarchWaves, 2) void k_march(
+    KParams P, const double* __restrict__ gin, double* __restrict__ gout,
+    const double* __restrict__ gw, int nstrips, int nseg, int h) {
+    const int n = nstrips * nseg;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int w = xcd_tile(blockIdx.x, gridDim.x) * kMarchWaves + wave;
+    if (w >= n) return;
+    const int seg = w / nstrips, strip = w - seg * nstrips;
+    const int y0 = P.y_lo + seg * h;
+    const int y1 = y0 + h - 1 < P.y_hi ? y0 + h - 1 : P.y_hi;
+    march_strip<kMarchSteps, GEO, EOS, VISC, DppLane>(P, gin, gout, gw,
+                                                      strip * march_cols(kMarchSteps), y0, y1,
+                                                      threadIdx.x & 63);
 }
 
 // psi pass of the two-pass schedule; also writes the mirrored ghost rows. PRE: gin holds
@@ -337,6 +359,80 @@ hipError_t launch_step2(const KParams& P, int tile2, const double* gin, double* 
         case 7: return launch_step2_t<32, 4, true>(P, gin, gout, gw, gmid, s);
         default: return launch_step2_t<64, 8>(P, gin, gout, gw, gmid, s);
     }
+}
+
+// Marching strips: the split into segments, and the launch.
+static int strips_of(const MarchShape& m) {
+    constexpr int C = march_cols(kMarchSteps);
+    return (m.nx + C - 1) / C;
+}
+
+// Rows per segment for `count` lattices, or 0 where the two-step tiles are faster. The split is
+// chosen by the time of one launch: every wave walks its segment's rows and the 4T-2 halo rows, the
+// SIMDs run one wave each or two at a time (a third round is a second pass over the chip, so the
+// number of waves should fall just below a multiple of 2048), and a launch costs about 7 us before
+// its first full row. Measured per row: 1.75 us with one wave per SIMD, 2.9 us for two
+// (2048 x 1024: 26 segments of 40 rows, 988 waves, 96 us per launch; 52 of 20, 1976 waves, 92 us;
+// 32 of 32, 1216 waves, 116 us). The two-step tiles make 49 updates per ns on a full chip. The
+// line lies near a million nodes: 1024 x 512 takes 11.3 us per step with tiles and 14.3 marching,
+// 1400 x 700 19.2 and 18.3, 1500 x 1001 27.7 and 24.0, 2048 x 1024 39.4 and 30.7, 4096 x 4096
+// 312 and 215.
+int march_rows(const MarchShape* m, int count) {
+    constexpr int H = 2 * kMarchSteps - 1;
+    int rmax = 0;
+    double nodes = 0.0;
+    for (int i = 0; i < count; ++i) {
+        if (m[i].rows < 16 || m[i].nx > (1 << 28)) return 0;
+        rmax = std::max(rmax, m[i].rows);
+        nodes += (double)m[i].nx * m[i].rows;
+    }
+    int best = 0;
+    double best_us = 0.0;
+    auto waves_at = [&](int h) {
+        long long n = 0;
+        for (int i = 0; i < count; ++i)
+            n += (long long)strips_of(m[i]) * ((m[i].rows + h - 1) / h);
+        return n;
+    };
+    for (int h = std::min(rmax, 1024); h >= 8; --h) {
+        const long long n = waves_at(h);
+        const double us = n <= kSimds ? 7.0 + 1.75 * (h + 2 * H)
+                                      : 7.0 + 2.9 * (h + 2 * H) * ((n + 2 * kSimds - 1) / (2 * kSimds));
+        if (!best || us < best_us) {
+            best = h;
+            best_us = us;
+        }
+    }
+    return best_us < 0.95 * (3.0 * nodes / 49000.0) ? best : 0;
+}
+
+void march_segments(const MarchShape& m, int inst, int y_lo, int h, std::vector<MarchSeg>* out) {
+    constexpr int C = march_cols(kMarchSteps);
+    const int nseg = (m.rows + h - 1) / h, hh = (m.rows + nseg - 1) / nseg;
+    for (int s = 0; s * hh < m.rows; ++s)
+        for (int x0 = 0; x0 < m.nx; x0 += C)
+            out->push_back({inst, x0, y_lo + s * hh, y_lo + std::min(m.rows, (s + 1) * hh) - 1});
+}
+
+hipError_t launch_march(const KParams& P, int h, const double* gin, double* gout, const double* gw,
+                        hipStream_t s) {
+    const int rows = P.y_hi - P.y_lo + 1;
+    const int nstrips = strips_of({P.nx, rows}), nseg = (rows + h - 1) / h;
+    const int blocks = (nstrips * nseg + kMarchWaves - 1) / kMarchWaves;
+    return dispatch(P, [&](auto geo, auto eos) {
+        constexpr int G = decltype(geo)::value, E = decltype(eos)::value;
+        if constexpr (G == GEO_MASK) {
+            return hipErrorInvalidValue;
+        } else {
+            if (P.visc_const)
+                hipLaunchKernelGGL((k_march<G, E, 1>), dim3(blocks), dim3(64 * kMarchWaves), 0, s,
+                                   P, gin, gout, gw, nstrips, nseg, h);
+            else
+                hipLaunchKernelGGL((k_march<G, E, 2>), dim3(blocks), dim3(64 * kMarchWaves), 0, s,
+                                   P, gin, gout, gw, nstrips, nseg, h);
+            return hipGetLastError();
+        }
+    });
 }
 
 // Fused tile shapes: 0-3 halo-recompute tiles TX x TY; 4-7 overlapped tiles 62 x TYI.
