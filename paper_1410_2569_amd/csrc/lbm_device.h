@@ -69,6 +69,49 @@ __device__ __forceinline__ int wrapx(int x, int nx) {
 // further down follow the same rule, so that every reverse-step tile (interior or not, of any
 // shape, single lattice or ensemble) gives the same gradient bits.
 
+// Quotient, reciprocal and square root of the time step, correctly rounded wherever operands and
+// results lie well inside the range of doubles (densities, pseudopotentials and velocities do):
+// Newton's iteration on the hardware's reciprocal (square root) estimate and a last correction by
+// the exact remainder (P. Markstein, "Computation of elementary functions on the IBM RISC
+// System/6000 processor", 1990). The compiler's own division and square root make the same
+// iterations, with the same bits, between steps that scale operands out of the denormal range and
+// put special values back: 4 and 3 instructions of 11 per division and 5 of 17 per square root,
+// all on the dependent chain. A zero divisor gives NaN here where those give an infinity; the
+// node is not finite either way.
+#ifdef __AMDGCN__
+__device__ __forceinline__ double recip(double b) {
+#pragma clang fp contract(off)
+    double y = __builtin_amdgcn_rcp(b);
+    y = fma(y, fma(-b, y, 1.0), y);
+    y = fma(y, fma(-b, y, 1.0), y);
+    return fma(fma(-b, y, 1.0), y, y);
+}
+__device__ __forceinline__ double quot(double a, double b) {
+#pragma clang fp contract(off)
+    double y = __builtin_amdgcn_rcp(b);
+    y = fma(y, fma(-b, y, 1.0), y);
+    y = fma(y, fma(-b, y, 1.0), y);
+    const double q = a * y;
+    return fma(fma(-b, q, a), y, q);
+}
+__device__ __forceinline__ double root(double x) {
+#pragma clang fp contract(off)
+    const double r = __builtin_amdgcn_rsq(x);
+    double g = x * r, h = r * 0.5;
+    const double d = fma(-h, g, 0.5);
+    g = fma(g, d, g);
+    h = fma(h, d, h);
+    g = fma(fma(-g, g, x), h, g);
+    g = fma(fma(-g, g, x), h, g);
+    // zeros and +infinity are their own roots
+    return __builtin_amdgcn_class(x, 0x260) ? x : g;
+}
+#else  // the host's own operations, where this header is compiled for the CPU
+__device__ __forceinline__ double recip(double b) { return 1.0 / b; }
+__device__ __forceinline__ double quot(double a, double b) { return a / b; }
+__device__ __forceinline__ double root(double x) { return sqrt(x); }
+#endif
+
 // p_EOS(rho) and psi(rho); a negative radicand yields NaN, caught by the observables. EOS selects
 // the equation of state compiled in (EOS_ANY: P.eos at run time).
 template <int EOS = EOS_ANY>
@@ -79,12 +122,12 @@ __device__ __forceinline__ double psi_of_rho(const KParams& P, double rho) {
         const double eta = P.b4 * rho;
         const double om = 1.0 - eta;
         const double num = fma(eta, fma(eta, om, 1.0), 1.0);  // 1 + eta + eta^2 - eta^3
-        p = fma(-P.a * rho, rho, (rho * P.RT) * num / (om * om * om));
+        p = fma(-P.a * rho, rho, quot((rho * P.RT) * num, om * om * om));
     } else {
         p = rho <= P.rho1 ? rho * P.th_v
           : (rho <= P.rho2 ? fma(rho - P.rho1, P.th_m, P.p1) : fma(rho - P.rho2, P.th_l, P.p2));
     }
-    return sqrt(P.two_over_G * (p - rho * (1.0 / 3.0)));
+    return root(P.two_over_G * (p - rho * (1.0 / 3.0)));
 }
 
 // Non-slip wet-node boundary (Sec. III.A) at a boundary node of the bottom wall plane: the
@@ -339,7 +382,7 @@ __device__ __forceinline__ void collide_force(const KParams& P, double f[9], dou
     const double m8 = s57 - s68;
 
     // Eq. (6): velocity with half the force
-    const double ir = 1.0 / rho;
+    const double ir = recip(rho);
     const double vx = fma(0.5, Fx, jx) * ir, vy = fma(0.5, Fy, jy) * ir;
     const double v2 = fma(vx, vx, vy * vy);
 
@@ -350,7 +393,7 @@ __device__ __forceinline__ void collide_force(const KParams& P, double f[9], dou
     } else {
         double phi = (rho - P.rho_v) * P.inv_drho;
         phi = fmin(fmax(phi, 0.0), 1.0);
-        snu = 1.0 / fma(3.0, fma(phi, P.dnu, P.nu_v), 0.5);
+        snu = recip(fma(3.0, fma(phi, P.dnu, P.nu_v), 0.5));
     }
     const double hnu = 1.0 - 0.5 * snu;
 

@@ -520,15 +520,15 @@ hipError_t launch_droplets(const KParams& P, const DropletArgs& D, double* rho, 
 }
 
 // The device's FP64 square root and division as the step kernels compile them: sq = sqrt(a),
-// quot = a / b, element-wise.
+// qt = a / b, element-wise.
 __global__ __launch_bounds__(256) void k_fp64_probe(const double* __restrict__ a,
                                                     const double* __restrict__ b,
                                                     double* __restrict__ sq,
-                                                    double* __restrict__ quot, long long n) {
+                                                    double* __restrict__ qt, long long n) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    sq[i] = sqrt(a[i]);
-    quot[i] = a[i] / b[i];
+    sq[i] = root(a[i]);
+    qt[i] = quot(a[i], b[i]);
 }
 
 hipError_t launch_fp64_probe(const double* a, const double* b, double* sq, double* quot,
