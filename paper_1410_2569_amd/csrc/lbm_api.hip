@@ -783,10 +783,7 @@ int lbm_observables_plane(lbm_ctx* c, double x_lo, double x_hi, double y_wall, l
     A.x_hi = x_hi;
     A.cx = std::isfinite(x_lo) && std::isfinite(x_hi) ? 0.5 * (x_lo + x_hi) : 0.5 * P.nx;
     A.cy = y_wall;
-    double* rho = c->g[c->cur ^ 1];  // the idle population buffer serves as scratch
-    hipError_t e = lbm::launch_rho_psi(P, c->g[c->cur], c->psi, rho, c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, "observables psi");
-    e = lbm::launch_obs(P, c->g[c->cur], rho, c->psi, c->gw, A, c->part, c->fin, c->stream);
+    hipError_t e = lbm::launch_obs(P, c->g[c->cur], c->gw, A, c->part, c->fin, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "observables");
     double q[32];
     e = host_copy(c->stream, q, c->fin, lbm::OBS_NQ * sizeof(double), hipMemcpyDeviceToHost);
@@ -848,6 +845,7 @@ int lbm_observables_of_state(const lbm_params* p, const double* d_f, const doubl
     const KParams P = kparams_of(p, L);
     const size_t plane_b = align_up((size_t)L.plane * sizeof(double), kAlign);
     const size_t part_b = align_up((size_t)lbm::obs_blocks(P) * lbm::OBS_NQ * sizeof(double), kAlign);
+    // (the size limit of the entry point, which holds two fields of the lattice as well)
     const size_t need = 2 * plane_b + part_b + align_up(32 * sizeof(double), kAlign);
     if (need > kStaticScratchBytes) {
         g_create_err = "observables_of_state: the lattice needs " + std::to_string(need) +
@@ -859,19 +857,9 @@ int lbm_observables_of_state(const lbm_params* p, const double* d_f, const doubl
     void* base = nullptr;
     hipError_t e = static_scratch(&base);
     if (e != hipSuccess) return create_fail(LBM_E_HIP, "observables_of_state: scratch address", e);
-    char* w = (char*)base;
-    double* rho = (double*)w;
-    double* psi = (double*)(w + plane_b);
-    double* part = (double*)(w + 2 * plane_b);
-    double* fin = (double*)(w + 2 * plane_b + part_b);
+    double* part = (double*)base;
+    double* fin = (double*)((char*)base + part_b);
     hipStream_t s = (hipStream_t)stream;
-    // the array keeps the previous call's contents: rows no kernel below writes must read 0
-    if (p->walls && !p->ghost_psi) {
-        e = lbm::launch_zero(psi, (size_t)p->nx * sizeof(double), s);
-        if (e == hipSuccess)
-            e = lbm::launch_zero(psi + (size_t)(p->ny - 1) * p->nx, (size_t)p->nx * sizeof(double), s);
-        if (e != hipSuccess) return create_fail(LBM_E_HIP, "observables_of_state: clear", e);
-    }
     lbm::ObsArgs A;
     const double yw = wall_plane(p->walls);
     A.rho_mid = 0.5 * (p->rho_l + p->rho_v);
@@ -880,8 +868,7 @@ int lbm_observables_of_state(const lbm_params* p, const double* d_f, const doubl
     A.x_hi = INFINITY;
     A.cx = 0.5 * P.nx;
     A.cy = yw;
-    e = lbm::launch_rho_psi(P, d_f, psi, rho, s, true);
-    if (e == hipSuccess) e = lbm::launch_obs(P, d_f, rho, psi, d_gw, A, part, fin, s, true);
+    e = lbm::launch_obs(P, d_f, d_gw, A, part, fin, s, true);
     double q[32];
     if (e == hipSuccess) e = host_copy(s, q, fin, lbm::OBS_NQ * sizeof(double), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return create_fail(LBM_E_HIP, "observables_of_state", e);
@@ -1147,7 +1134,9 @@ struct lbm_batch {
     lbm::MarchSeg* d_segs;  // work-list of the marching strips
     int nsegs;              // 0: schedule 2 runs tiles
     int visc;               // as in launch_batch_march
-    std::vector<double*> psi, part, fin;
+    double* d_obs;          // 16 sums per instance, then the contact planes
+    int obs_blocks;         // most blocks of an instance's observables
+    std::vector<double*> part, fin;
     int ntiles;
     int cur;
     int64_t step;
@@ -1188,7 +1177,7 @@ static int spin_limit_from_env() {
 }
 
 struct BatchLayout {
-    size_t off_desc, off_tiles, off_bar, off_rows, off_segs, total;
+    size_t off_desc, off_tiles, off_bar, off_rows, off_segs, off_obs, total;
     std::vector<lbm::MarchSeg> segs;  // schedule 2 marches these strips (none: tiles)
     std::vector<size_t> off_inst;  // per instance: g0, g1, gw, psi, part, fin
     std::vector<Layout> L;
@@ -1229,6 +1218,8 @@ bool batch_layout(const lbm_params* p, int32_t count, int tile, BatchLayout* B) 
                 lbm::march_segments(shapes[i], i, y_lo_of(&p[i]), h, &B->segs);
     }
     o += align_up(B->segs.size() * sizeof(lbm::MarchSeg), kAlign);
+    B->off_obs = o;  // observables: 16 sums per instance, then the contact planes
+    o += align_up((size_t)count * 17 * sizeof(double), kAlign);
     B->off_inst.resize(count);
     for (int i = 0; i < count; ++i) {
         B->off_inst[i] = o;
@@ -1311,6 +1302,8 @@ static int batch_create_impl(const lbm_params* p, int32_t count,
     b->d_rows = (int*)(b->ws + B.off_rows);
     b->d_segs = (lbm::MarchSeg*)(b->ws + B.off_segs);
     b->nsegs = (int)B.segs.size();
+    b->d_obs = (double*)(b->ws + B.off_obs);
+    b->obs_blocks = 0;
     b->cur = 0;
     b->step = 0;
     b->tune = tn;
@@ -1340,8 +1333,9 @@ static int batch_create_impl(const lbm_params* p, int32_t count,
         d.tile0 = B.tile0[i];
         d.ntx = B.ntx[i];
         d.nty = B.nty[i];
+        d.part = (double*)(base + L.off_part);
         b->desc.push_back(d);
-        b->psi.push_back((double*)(base + L.off_psi));
+        b->obs_blocks = std::max(b->obs_blocks, lbm::obs_tiles(kp));
         b->part.push_back((double*)(base + L.off_part));
         b->fin.push_back((double*)(base + L.off_fin));
         for (int t = 0; t < B.ntx[i] * B.nty[i]; ++t) tile_inst[B.tile0[i] + t] = i;
@@ -1540,6 +1534,7 @@ int lbm_batch_step(lbm_batch* b, int64_t n) {
 }
 
 static int batch_check_abort(lbm_batch* b) {
+    if (b->tune.schedule != 1) return LBM_OK;  // only the persistent kernel raises the flag
     int flag = 0;
     hipError_t e = host_copy(b->stream, &flag, b->d_flag, sizeof(int), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "flag read");
@@ -1554,34 +1549,25 @@ int lbm_batch_observables_plane(lbm_batch* b, const double* y_wall, lbm_obs* out
             if (!std::isfinite(y_wall[i])) return LBM_E_INVAL;
     int rc = batch_check_abort(b);
     if (rc) return rc;
-    std::vector<double> q((size_t)b->count * 32);
-    std::vector<lbm::ObsArgs> args(b->count);
-    for (int i = 0; i < b->count; ++i) {
-        const KParams& P = b->kp[i];
-        const lbm::InstDesc& d = b->desc[i];
-        lbm::ObsArgs& A = args[i];
-        const double yw = y_wall ? y_wall[i] : wall_plane(b->p[i].walls);
-        A.rho_mid = 0.5 * (b->p[i].rho_l + b->p[i].rho_v);
-        A.y_min = yw + 3.0;
-        A.x_lo = -INFINITY;
-        A.x_hi = INFINITY;
-        A.cx = 0.5 * P.nx;
-        A.cy = yw;
-        double* rho = d.g[b->cur ^ 1];
-        hipError_t e = lbm::launch_rho_psi(P, d.g[b->cur], b->psi[i], rho, b->stream);
-        if (e == hipSuccess)
-            e = lbm::launch_obs(P, d.g[b->cur], rho, b->psi[i], d.gw, A, b->part[i], b->fin[i],
-                                b->stream);
-        if (e == hipSuccess)
-            e = host_copy(b->stream, q.data() + (size_t)i * 32, b->fin[i],
-                          lbm::OBS_NQ * sizeof(double), hipMemcpyDeviceToHost);
-        if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "batch observables");
+    const size_t n = (size_t)b->count;
+    double* d_yw = nullptr;
+    hipError_t e = hipSuccess;
+    if (y_wall) {
+        d_yw = b->d_obs + 16 * n;
+        e = host_copy(b->stream, d_yw, y_wall, n * sizeof(double), hipMemcpyHostToDevice);
+        if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "batch observables planes");
     }
-    hipError_t e = hipStreamSynchronize(b->stream);
-    if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "batch observables sync");
+    std::vector<double> q(16 * n);
+    e = lbm::launch_batch_obs(b->d_inst, b->count, b->obs_blocks, d_yw, b->cur, b->d_obs, b->stream);
+    if (e == hipSuccess)
+        e = host_copy(b->stream, q.data(), b->d_obs, 16 * n * sizeof(double), hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "batch observables");
     int bad = 0;
     for (int i = 0; i < b->count; ++i) {
-        obs_from_sums(q.data() + (size_t)i * 32, args[i], b->step, &out[i]);
+        lbm::ObsArgs A{};
+        A.cx = 0.5 * b->p[i].nx;
+        A.cy = y_wall ? y_wall[i] : wall_plane(b->p[i].walls);
+        obs_from_sums(q.data() + 16 * (size_t)i, A, b->step, &out[i]);
         bad |= out[i].nonfinite != 0;
     }
     return bad ? LBM_E_NONFINITE : LBM_OK;

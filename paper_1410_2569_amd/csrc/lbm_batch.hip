@@ -17,6 +17,7 @@
 #include "lbm_device.h"
 #include "lbm_internal.h"
 #include "lbm_march.h"
+#include "lbm_obs.h"
 #include "lbm_wave.h"
 
 namespace lbm {
@@ -280,6 +281,29 @@ __global__ __launch_bounds__(256) void k_batch_contact_line(const InstDesc* __re
                                                             double* __restrict__ out) {
     const InstDesc* D = inst + blockIdx.x;
     contact_line_block(D->P, D->g[cur], rows[blockIdx.x], D->P.rho_mid, out + 2 * blockIdx.x);
+}
+
+// Observables of every instance in two launches: blockIdx.y is the instance, blocks past its tiles
+// have nothing to do. The arithmetic and its order are those of the lattice alone.
+__global__ __launch_bounds__(256) void k_batch_obs(const InstDesc* __restrict__ inst,
+                                                   const double* __restrict__ y_wall, int cur) {
+    __shared__ ObsLds lds;
+    const InstDesc* D = inst + blockIdx.y;
+    const KParams& P = D->P;
+    const int nbx = (P.nx + 63) / 64, nby = (P.y_hi - P.y_lo + kObsRows) / kObsRows;
+    if ((int)blockIdx.x >= nbx * nby) return;
+    const double yw = y_wall ? y_wall[blockIdx.y] : (P.wet ? 1.0 : 0.5);
+    const ObsArgs A{P.rho_mid, yw + 3.0, -__builtin_huge_val(), __builtin_huge_val(),
+                    0.5 * P.nx, yw};
+    obs_tile<false>(P, gptr(D->g[cur]), gptr(D->gw), A, blockIdx.x % nbx, blockIdx.x / nbx, nbx,
+                    gptr(D->part), lds);
+}
+
+__global__ __launch_bounds__(256) void k_batch_obs_final(const InstDesc* __restrict__ inst,
+                                                         double* __restrict__ out) {
+    __shared__ double sh[O_NQ][256];
+    const InstDesc* D = inst + blockIdx.x;
+    obs_final_block(gptr(D->part), obs_rows(D->P), sh, out + 16 * blockIdx.x);
 }
 
 // ---- ensemble adjoint ---------------------------------------------------------------------------
@@ -555,6 +579,19 @@ hipError_t launch_batch_march(int geo, int eos, int visc, const InstDesc* inst,
             return go(std::integral_constant<int, 0>{});
         }
     });
+}
+
+int obs_tiles(const KParams& P) {
+    return (P.nx + 63) / 64 * ((P.y_hi - P.y_lo + kObsRows) / kObsRows);
+}
+
+hipError_t launch_batch_obs(const InstDesc* inst, int count, int max_blocks, const double* y_wall,
+                            int cur, double* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_batch_obs, dim3(max_blocks, count), dim3(256), 0, s, inst, y_wall, cur);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_batch_obs_final, dim3(count), dim3(256), 0, s, inst, out);
+    return hipGetLastError();
 }
 
 hipError_t launch_batch_contact_line(const InstDesc* inst, const int* rows, int count, int cur,

@@ -540,36 +540,25 @@ __device__ __forceinline__ double op_identity(int q) {
 
 __device__ __forceinline__ void add_point(double v[O_NQ], double px, double py, double cx,
                                           double cy) {
+#pragma clang fp contract(off)
     const double X = px - cx, Y = py - cy, r2 = X * X + Y * Y;
     v[O_N] += 1.0; v[O_SX] += X; v[O_SY] += Y; v[O_SXX] += X * X; v[O_SYY] += Y * Y;
     v[O_SXY] += X * Y; v[O_SXR] += X * r2; v[O_SYR] += Y * r2; v[O_SR] += r2;
 }
 
-// Observables contribution of node (x, y) (x < nx, y_lo <= y <= y_hi) to v[O_NQ]: its density,
-// velocity of Eq. (6) (forces from psi_g, the psi field with its ghost rows), and the rho_mid
-// crossings on the edges to its right and upper neighbours. rho_f: density of every fluid node.
-// Solid nodes of a mask contribute nothing. PRE: gin holds pre-collision populations (see
-// node_populations).
-template <bool PRE = false>
-__device__ __forceinline__ void obs_node(const KParams& P, const double* __restrict__ gin,
-                                         const double* __restrict__ rho_f,
-                                         const double* __restrict__ psi_g,
-                                         const double* __restrict__ gw, const ObsArgs& A, int x,
-                                         int y, double v[O_NQ]) {
-    if (is_solid_node(P, x, y)) return;
-    const long long i = (long long)y * P.pitch + x;
-    double f[9];
-    node_populations<PRE>(P, gin, x, y, f);
-    const double rho = rho_f[i], pc = psi_g[i];
-    const int xm = x == 0 ? P.nx - 1 : x - 1, xp = x == P.nx - 1 ? 0 : x + 1;
-    int ym = y - 1, yp = y + 1;
-    if (!P.walls || P.mask) { ym = wrapx(ym, P.ny); yp = wrapx(yp, P.ny); }
-    const double* rm = psi_g + (long long)ym * P.pitch;
-    const double* r0 = psi_g + (long long)y * P.pitch;
-    const double* rp = psi_g + (long long)yp * P.pitch;
+// Observables contribution of a fluid node (x, y) to v[O_NQ]: its density, velocity of Eq. (6) and
+// the rho_mid crossings on the edges to its right and upper neighbours. f: its pre-collision
+// populations; w: psi of its 3 x 3 neighbourhood (rows from below); rr, ru: density of the right
+// and upper neighbour, read only where that is a fluid node of the lattice.
+__device__ __forceinline__ void obs_values(const KParams& P, const double f[9], double rho,
+                                           const double w[9], const double* __restrict__ gw,
+                                           const ObsArgs& A, int x, int y, double rr, double ru,
+                                           double v[O_NQ]) {
+#pragma clang fp contract(off)
+    const double pc = w[4];
     double sx, sy, Ax = 0.0, Ay = 0.0, vx, vy;
-    cohesion_sum(rm[xm], rm[x], rm[xp], r0[xm], r0[xp], rp[xm], rp[x], rp[xp], sx, sy);
-    if (P.mask) adhesion_mask(P, x, y, P.links[(unsigned)i], Ax, Ay);
+    cohesion_sum(w[0], w[1], w[2], w[3], w[5], w[6], w[7], w[8], sx, sy);
+    if (P.mask) adhesion_mask(P, x, y, P.links[(unsigned)y * P.pitch + x], Ax, Ay);
     else adhesion_sum(P, gw, x, y, Ax, Ay);
     velocity(P, f, rho, pc, sx, sy, Ax, Ay, vx, vy);
     const double u = sqrt(vx * vx + vy * vy);
@@ -582,21 +571,45 @@ __device__ __forceinline__ void obs_node(const KParams& P, const double* __restr
     // interface crossings on the edges to the right and upper neighbours
     const bool la = rho >= A.rho_mid;
     if (x + 1 < P.nx && !is_solid_node(P, x + 1, y)) {
-        const double rb = rho_f[i + 1];
-        if ((rb >= A.rho_mid) != la) {
-            const double t = (A.rho_mid - rho) / (rb - rho);
+        if ((rr >= A.rho_mid) != la) {
+            const double t = (A.rho_mid - rho) / (rr - rho);
             const double px = x + t, py = (double)y;
             if (py >= A.y_min && px >= A.x_lo && px < A.x_hi) add_point(v, px, py, A.cx, A.cy);
         }
     }
     if (y + 1 <= P.y_hi && !is_solid_node(P, x, y + 1)) {
-        const double rb = rho_f[i + P.pitch];
-        if ((rb >= A.rho_mid) != la) {
-            const double t = (A.rho_mid - rho) / (rb - rho);
+        if ((ru >= A.rho_mid) != la) {
+            const double t = (A.rho_mid - rho) / (ru - rho);
             const double px = (double)x, py = y + t;
             if (py >= A.y_min && px >= A.x_lo && px < A.x_hi) add_point(v, px, py, A.cx, A.cy);
         }
     }
+}
+
+// Observables contribution of node (x, y) (x < nx, y_lo <= y <= y_hi) to v[O_NQ] from fields of
+// [ny][pitch] doubles: rho_f, the density of every fluid node, and psi_g, psi with its ghost rows.
+// Solid nodes of a mask contribute nothing. PRE: gin holds pre-collision populations (see
+// node_populations).
+template <bool PRE = false>
+__device__ __forceinline__ void obs_node(const KParams& P, const double* __restrict__ gin,
+                                         const double* __restrict__ rho_f,
+                                         const double* __restrict__ psi_g,
+                                         const double* __restrict__ gw, const ObsArgs& A, int x,
+                                         int y, double v[O_NQ]) {
+    if (is_solid_node(P, x, y)) return;
+    const long long i = (long long)y * P.pitch + x;
+    double f[9];
+    node_populations<PRE>(P, gin, x, y, f);
+    const int xm = x == 0 ? P.nx - 1 : x - 1, xp = x == P.nx - 1 ? 0 : x + 1;
+    int ym = y - 1, yp = y + 1;
+    if (!P.walls || P.mask) { ym = wrapx(ym, P.ny); yp = wrapx(yp, P.ny); }
+    const double* rm = psi_g + (long long)ym * P.pitch;
+    const double* r0 = psi_g + (long long)y * P.pitch;
+    const double* rp = psi_g + (long long)yp * P.pitch;
+    const double w[9] = {rm[xm], rm[x], rm[xp], r0[xm], r0[x], r0[xp], rp[xm], rp[x], rp[xp]};
+    const double rr = x + 1 < P.nx ? rho_f[i + 1] : 0.0;
+    const double ru = y + 1 <= P.y_hi ? rho_f[i + P.pitch] : 0.0;
+    obs_values(P, f, rho_f[i], w, gw, A, x, y, rr, ru, v);
 }
 
 // XCD-aware tile order: workgroup i runs on XCD i mod 8; give each XCD a contiguous range of

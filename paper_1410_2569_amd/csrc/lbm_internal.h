@@ -15,6 +15,7 @@ struct InstDesc {
     KParams P;
     double* g[2];  // population buffers (post-collision), ping-pong
     double* gw;    // [2][pitch] G_w
+    double* part;  // partial rows of the observables
     int tile0;     // first tile of this instance in the flattened work-list
     int ntx, nty;  // tiles in x and y
     int pad;
@@ -89,15 +90,15 @@ hipError_t launch_pull(const KParams& P, const double* gin, double* fout, hipStr
 hipError_t launch_repack(const double* src, long long src_plane, int src_pitch, double* dst,
                          long long dst_plane, int dst_pitch, int nx, int ny, int planes,
                          hipStream_t s);
-// pre: gin holds pre-collision populations (otherwise the post-collision state, pulled)
 hipError_t launch_rho_psi(const KParams& P, const double* gin, double* psi, double* rho,
-                          hipStream_t s, bool pre = false);
+                          hipStream_t s);
 hipError_t launch_contact_line(const KParams& P, const double* gin, int row, double mid,
                                double* out, hipStream_t s);
 int obs_blocks(const KParams& P);
-hipError_t launch_obs(const KParams& P, const double* gin, const double* rho, const double* psi,
-                      const double* gw, const ObsArgs& A, double* part, double* out,
-                      hipStream_t s, bool pre = false);
+// part: obs_blocks(P) rows of OBS_NQ doubles. pre: gin holds pre-collision populations (otherwise
+// the post-collision state, pulled)
+hipError_t launch_obs(const KParams& P, const double* gin, const double* gw, const ObsArgs& A,
+                      double* part, double* out, hipStream_t s, bool pre = false);
 
 // adjoint
 hipError_t launch_adj(const KParams& P, const AdjPtrs& A, hipStream_t s);
@@ -134,6 +135,11 @@ hipError_t launch_batch_persistent(int tile, int geo, int eos, int grid, const I
                                    hipStream_t s);
 hipError_t launch_batch_contact_line(const InstDesc* inst, const int* rows, int count, int cur,
                                      double* out, hipStream_t s);
+// Observables of every instance: out[16 i + q] for instance i, with the contact planes y_wall
+// (device array; null: the default planes). max_blocks: the most obs_tile blocks of an instance.
+int obs_tiles(const KParams& P);
+hipError_t launch_batch_obs(const InstDesc* inst, int count, int max_blocks, const double* y_wall,
+                            int cur, double* out, hipStream_t s);
 int batch_persistent_occupancy(int tile);
 // ensemble adjoint, over work-lists of the tiles of every instance (bounce-back walls):
 // recomputation of segment states i -> i+1, i+2 (two steps, 64 x 8 output tiles) or i -> i+1 (one

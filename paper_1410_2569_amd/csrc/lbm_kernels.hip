@@ -19,6 +19,7 @@
 #include "lbm_device.h"
 #include "lbm_internal.h"
 #include "lbm_march.h"
+#include "lbm_obs.h"
 #include "lbm_wave.h"
 
 namespace lbm {
@@ -121,16 +122,14 @@ __global__ __launch_bounds__(64 * kMarchWaves, 2) void k_march(
                                                       threadIdx.x & 63);
 }
 
-// psi pass of the two-pass schedule; also writes the mirrored ghost rows. PRE: gin holds
-// pre-collision populations.
-template <bool PRE = false>
+// psi pass of the two-pass schedule and density read-out; also writes the mirrored ghost rows.
 __global__ __launch_bounds__(256) void k_psi(KParams P, const double* __restrict__ gin,
                                              double* __restrict__ psi_g,
                                              double* __restrict__ rho_out) {
     const int x = blockIdx.x * 64 + (threadIdx.x & 63);
     const int y = P.y_lo + blockIdx.y * 4 + (threadIdx.x >> 6);
     if (x >= P.nx || y > P.y_hi) return;
-    psi_node<PRE>(P, gin, psi_g, rho_out, x, y);
+    psi_node(P, gin, psi_g, rho_out, x, y);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -195,65 +194,20 @@ __global__ __launch_bounds__(256) void k_repack(const double* __restrict__ src, 
 }
 
 // ------------------------------------------------------------------------------------------------
-// Observables: per-block partials (wave-level shuffles, then LDS across waves), fixed-order final
-// reduction. No floating-point atomics, so results are bitwise reproducible.
+// Observables (obs_tile, obs_final_block)
 // ------------------------------------------------------------------------------------------------
-// Block of 256 threads over a 64 x 4 patch. rho_f: rho of every fluid node (from k_psi);
-// psi_g: psi with ghost rows. Writes O_NQ partials per block. PRE: gin holds pre-collision
-// populations.
-template <bool PRE = false>
+template <bool PRE>
 __global__ __launch_bounds__(256) void k_obs(KParams P, const double* __restrict__ gin,
-                                             const double* __restrict__ rho_f,
-                                             const double* __restrict__ psi_g,
                                              const double* __restrict__ gw, ObsArgs A,
                                              double* __restrict__ part) {
-    const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = P.y_lo + blockIdx.y * 4 + (threadIdx.x >> 6);
-    double v[O_NQ];
-    for (int q = 0; q < O_NQ; ++q) v[q] = op_identity(q);
-    if (x < P.nx && y <= P.y_hi) obs_node<PRE>(P, gin, rho_f, psi_g, gw, A, x, y, v);
-    // wave-level tree (xor shuffles), then across the 4 waves of the block
-    __shared__ double red[4][O_NQ];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int q = 0; q < O_NQ; ++q) {
-        double s = v[q];
-        for (int off = 32; off > 0; off >>= 1) s = op_combine(q, s, __shfl_xor(s, off, 64));
-        if (lane == 0) red[wv][q] = s;
-    }
-    __syncthreads();
-    if (threadIdx.x < O_NQ) {
-        const int q = threadIdx.x;
-        double s = op_combine(q, op_combine(q, red[0][q], red[1][q]),
-                              op_combine(q, red[2][q], red[3][q]));
-        part[(long long)(blockIdx.y * gridDim.x + blockIdx.x) * O_NQ + q] = s;
-    }
+    __shared__ ObsLds lds;
+    obs_tile<PRE>(P, gin, gw, A, blockIdx.x, blockIdx.y, gridDim.x, part, lds);
 }
 
-// One block of 256 threads: for every quantity, thread t combines partials t, t+256, ... in
-// order, then a fixed tree; all quantities advance together (one pass over the partial rows).
 __global__ __launch_bounds__(256) void k_obs_final(const double* __restrict__ part, int nblk,
                                                    double* __restrict__ out) {
     __shared__ double sh[O_NQ][256];
-    double s[O_NQ];
-#pragma unroll
-    for (int q = 0; q < O_NQ; ++q) s[q] = op_identity(q);
-    for (int b = threadIdx.x; b < nblk; b += 256) {
-        const double* r = part + (long long)b * O_NQ;
-#pragma unroll
-        for (int q = 0; q < O_NQ; ++q) s[q] = op_combine(q, s[q], r[q]);
-    }
-#pragma unroll
-    for (int q = 0; q < O_NQ; ++q) sh[q][threadIdx.x] = s[q];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) {
-#pragma unroll
-            for (int q = 0; q < O_NQ; ++q)
-                sh[q][threadIdx.x] = op_combine(q, sh[q][threadIdx.x], sh[q][threadIdx.x + w]);
-        }
-        __syncthreads();
-    }
-    if ((int)threadIdx.x < O_NQ) out[threadIdx.x] = sh[threadIdx.x][0];
+    obs_final_block(part, nblk, sh, out);
 }
 
 // Contact line of one lattice (contact_line_block).
@@ -450,7 +404,7 @@ void tile_shape(int tile, int* tx, int* ty) {
 hipError_t launch_step(const KParams& P, int schedule, int tile, const double* gin, double* gout,
                        double* psi, const double* gw, hipStream_t s) {
     if (schedule == 1) {
-        hipLaunchKernelGGL(k_psi<false>, node_grid(P), dim3(256), 0, s, P, gin, psi,
+        hipLaunchKernelGGL(k_psi, node_grid(P), dim3(256), 0, s, P, gin, psi,
                            (double*)nullptr);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -562,9 +516,8 @@ hipError_t launch_repack(const double* src, long long src_plane, int src_pitch, 
 }
 
 hipError_t launch_rho_psi(const KParams& P, const double* gin, double* psi, double* rho,
-                          hipStream_t s, bool pre) {
-    if (pre) hipLaunchKernelGGL(k_psi<true>, node_grid(P), dim3(256), 0, s, P, gin, psi, rho);
-    else hipLaunchKernelGGL(k_psi<false>, node_grid(P), dim3(256), 0, s, P, gin, psi, rho);
+                          hipStream_t s) {
+    hipLaunchKernelGGL(k_psi, node_grid(P), dim3(256), 0, s, P, gin, psi, rho);
     return hipGetLastError();
 }
 
@@ -574,20 +527,16 @@ hipError_t launch_contact_line(const KParams& P, const double* gin, int row, dou
     return hipGetLastError();
 }
 
-int obs_blocks(const KParams& P) {
-    dim3 g = node_grid(P);
-    return (int)(g.x * g.y);
-}
+int obs_blocks(const KParams& P) { return obs_rows(P); }
 
-hipError_t launch_obs(const KParams& P, const double* gin, const double* rho, const double* psi,
-                      const double* gw, const ObsArgs& A, double* part, double* out,
-                      hipStream_t s, bool pre) {
-    dim3 g = node_grid(P);
-    if (pre) hipLaunchKernelGGL(k_obs<true>, g, dim3(256), 0, s, P, gin, rho, psi, gw, A, part);
-    else hipLaunchKernelGGL(k_obs<false>, g, dim3(256), 0, s, P, gin, rho, psi, gw, A, part);
+hipError_t launch_obs(const KParams& P, const double* gin, const double* gw, const ObsArgs& A,
+                      double* part, double* out, hipStream_t s, bool pre) {
+    const dim3 g((P.nx + 63) / 64, (P.y_hi - P.y_lo + kObsRows) / kObsRows);
+    if (pre) hipLaunchKernelGGL(k_obs<true>, g, dim3(256), 0, s, P, gin, gw, A, part);
+    else hipLaunchKernelGGL(k_obs<false>, g, dim3(256), 0, s, P, gin, gw, A, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_obs_final, dim3(1), dim3(256), 0, s, part, (int)(g.x * g.y), out);
+    hipLaunchKernelGGL(k_obs_final, dim3(1), dim3(256), 0, s, part, obs_rows(P), out);
     return hipGetLastError();
 }
 
