@@ -34,6 +34,7 @@ struct lbm_ctx {
     int schedule;
     int tile;
     int tile2;  // output tile of the two-step kernel
+    int steps;  // tile of the multi-step kernel, which schedule 2 then uses first; -1: none
     int march;  // rows per segment of the marching strips, which schedule 2 then uses; 0: tiles
     // last lbm_forward_ckpt: where it started, its length and checkpoint interval
     int64_t adj_start, adj_nsteps;
@@ -575,6 +576,7 @@ static int create_impl(const lbm_params* p, const uint8_t* solid, const double* 
     // 256x128 7.35 / 6.74 / 5.78, 384x192 7.76 / 8.58 / 7.98, 512x256 8.39 / 9.44 / 10.56.
     c->tile2 = ((p->nx + 31) / 32) * ((y_hi_of(p) - y_lo_of(p) + 4) / 4) <= 384 ? 7 : 0;
     const lbm::MarchShape shape{p->nx, y_hi_of(p) - y_lo_of(p) + 1};
+    c->steps = lbm::steps_tile_of(shape.nx, shape.rows);
     c->march = solid ? 0 : lbm::march_rows(&shape, 1);
     c->adj_start = -1;
     c->adj_nsteps = 0;
@@ -674,16 +676,24 @@ int lbm_set_schedule(lbm_ctx* c, int32_t schedule) {
         c->schedule = 2;
         c->tile2 = schedule - 32;
         c->march = 0;
+        c->steps = -1;
         return LBM_OK;
     }
     return fail(c, LBM_E_INVAL, "unknown schedule");
 }
 
 // Launches of `n` steps of the context's schedule from buffer parity `cur`; *cur_out receives the
-// parity holding the result (every launch swaps the buffers: two steps per launch make n/2 + n%2
-// swaps, single steps n).
+// parity holding the result (every launch swaps the buffers).
 static hipError_t enqueue_steps(lbm_ctx* c, int64_t n, int cur, hipStream_t s, int* cur_out) {
     *cur_out = cur;
+    if (c->schedule == 2 && c->steps >= 0) {
+        for (; n >= lbm::kTileSteps; n -= lbm::kTileSteps) {
+            hipError_t e = lbm::launch_steps(c->kp, c->steps, c->g[cur], c->g[cur ^ 1], c->gw, s);
+            if (e != hipSuccess) return e;
+            cur ^= 1;
+            *cur_out = cur;
+        }
+    }
     if (c->schedule == 2 && c->march) {
         // a remainder of one step is left to two two-step launches
         for (; n >= 3 && n != 4; n -= 3) {
@@ -1075,7 +1085,11 @@ int lbm_backward(lbm_ctx* c, int64_t nsteps, int32_t K, void* d_adj, size_t byte
                                       hipMemcpyDeviceToDevice, a);
         const int64_t len = seg_len(j);
         int64_t i = 0;
-        // two steps per launch, the first one written too
+        // four or two steps per launch, those before the last written too
+        if (c->steps >= 0)
+            for (; i + lbm::kTileSteps <= len - 1 && r == hipSuccess; i += lbm::kTileSteps)
+                r = lbm::launch_steps(P, c->steps, seg(j, i), seg(j, i + lbm::kTileSteps), c->gw, a,
+                                      seg(j, i + 1), (long long)(A.fbytes / sizeof(double)));
         for (; i + 2 <= len - 1 && r == hipSuccess; i += 2)
             r = lbm::launch_step2(P, c->tile2, seg(j, i), seg(j, i + 2), c->gw, a, seg(j, i + 1));
         if (i + 1 <= len - 1 && r == hipSuccess)

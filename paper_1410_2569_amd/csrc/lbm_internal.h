@@ -69,6 +69,16 @@ hipError_t launch_march(const KParams& P, int h, const double* gin, double* gout
 // visc: 1 every instance has one viscosity, 2 none has, 0 some have
 hipError_t launch_batch_march(int geo, int eos, int visc, const InstDesc* inst,
                               const MarchSeg* segs, int n, int cur, hipStream_t s);
+// Multi-step tiles (lbm_steps.h): kTileSteps steps per launch on lattices too small to fill the GPU.
+constexpr int kTileSteps = 4;
+// Tile of a lattice of nx columns and `rows` fluid rows (for launch_steps), or -1 where the
+// two-step tiles are the better choice.
+int steps_tile_of(int nx, int rows);
+// mid (optional, bounce-back or periodic rows): receives the states after steps 1 .. 3, mstride
+// doubles apart.
+hipError_t launch_steps(const KParams& P, int tile, const double* gin, double* gout,
+                        const double* gw, hipStream_t s, double* mid = nullptr,
+                        long long mstride = 0);
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);  // bytes and p 8-byte aligned
 hipError_t launch_init(const KParams& P, const double* rho0, double* g, hipStream_t s);
 // droplets of the initial state (lbm_create_droplets): up to kMaxDroplets tanh profiles

@@ -9,6 +9,7 @@
 //   two-pass  psi pass (pull, rho, psi -> psi array with mirrored ghost rows), then the step
 //             kernel stages the psi tile plus halo in LDS: 72 + 8 B and 72 + 8 + 72 B per update.
 //   two-step  two time steps per launch with the intermediate state in LDS (step2_tile).
+//   multi-step four time steps per launch on lattices too small to fill the GPU (steps_tile).
 //   marching  three time steps per launch on large lattices: strips of columns march through
 //             registers (march_strip).
 // With the wet-node wall scheme the boundary nodes also write their force (16 B) to the solid row,
@@ -20,6 +21,7 @@
 #include "lbm_internal.h"
 #include "lbm_march.h"
 #include "lbm_obs.h"
+#include "lbm_steps.h"
 #include "lbm_wave.h"
 
 namespace lbm {
@@ -102,6 +104,19 @@ __global__ __launch_bounds__(NTH, NTH == step2_threads(TX, TY, GEO)
     const int tile = xcd_tile(blockIdx.x, ntx * nty);
     step2_tile_any<TX, TY, GEO, EOS, MID, false, NTH>(P, gin, gout, gw, (tile % ntx) * TX,
                                                       P.y_lo + (tile / ntx) * TY, lds, gmid);
+}
+
+// kTileSteps steps per launch over TX x TY output tiles (steps_tile).
+template <int TX, int TY, int GEO, int EOS, bool MID>
+__global__ __launch_bounds__(steps_threads(kTileSteps, TX, TY)) void k_steps(
+    KParams P, const double* __restrict__ gin, double* __restrict__ gout,
+    const double* __restrict__ gw, double* __restrict__ mid, long long mstride) {
+    __shared__ StepsLds<kTileSteps, TX, TY, GEO> lds;
+    const int ntx = (P.nx + TX - 1) / TX;
+    const int nty = (P.y_hi - P.y_lo + TY) / TY;
+    const int t = xcd_tile(blockIdx.x, ntx * nty);
+    steps_tile<kTileSteps, TX, TY, GEO, EOS, MID>(P, gin, gout, gw, (t % ntx) * TX,
+                                                  P.y_lo + (t / ntx) * TY, lds, mid, mstride);
 }
 
 // kMarchSteps steps per launch: every wave marches one strip through one segment of h rows
@@ -312,6 +327,49 @@ hipError_t launch_step2(const KParams& P, int tile2, const double* gin, double* 
         case 6: return launch_step2_t<64, 4, true>(P, gin, gout, gw, gmid, s);
         case 7: return launch_step2_t<32, 4, true>(P, gin, gout, gw, gmid, s);
         default: return launch_step2_t<64, 8>(P, gin, gout, gw, gmid, s);
+    }
+}
+
+// Multi-step tiles. The smallest tile that gives every compute unit at most one workgroup (the
+// halo's work per workgroup is then the least), or 16 x 8 up to two per compute unit: 300 x 150 (361
+// tiles) 3.47 -> 3.18 us per step, 340 x 140 (396) 3.87 -> 3.23. Beyond, the halo's work tells:
+// 384 x 192 (576 tiles) 3.82 -> 4.39.
+int steps_tile_of(int nx, int rows) {
+    auto tiles = [&](int tx, int ty) { return (long long)((nx + tx - 1) / tx) * ((rows + ty - 1) / ty); };
+    if (tiles(8, 4) <= 256) return 0;
+    if (tiles(8, 8) <= 256) return 1;
+    return tiles(16, 8) <= 512 ? 2 : -1;
+}
+
+template <int TX, int TY>
+static hipError_t launch_steps_t(const KParams& P, const double* gin, double* gout,
+                                 const double* gw, double* mid, long long mstride, hipStream_t s) {
+    const int ntx = (P.nx + TX - 1) / TX;
+    const int nty = (P.y_hi - P.y_lo + TY) / TY;
+    return dispatch(P, [&](auto geo, auto eos) {
+        constexpr int G = decltype(geo)::value, E = decltype(eos)::value;
+        constexpr int NT = steps_threads(kTileSteps, TX, TY);
+        if (!mid) {
+            hipLaunchKernelGGL((k_steps<TX, TY, G, E, false>), dim3(ntx * nty), dim3(NT), 0, s, P,
+                               gin, gout, gw, mid, mstride);
+            return hipGetLastError();
+        }
+        if constexpr (G == GEO_ROWS) {
+            hipLaunchKernelGGL((k_steps<TX, TY, G, E, true>), dim3(ntx * nty), dim3(NT), 0, s, P,
+                               gin, gout, gw, mid, mstride);
+            return hipGetLastError();
+        } else {
+            return hipErrorInvalidValue;
+        }
+    });
+}
+
+hipError_t launch_steps(const KParams& P, int tile, const double* gin, double* gout,
+                        const double* gw, hipStream_t s, double* mid, long long mstride) {
+    switch (tile) {
+        case 0: return launch_steps_t<8, 4>(P, gin, gout, gw, mid, mstride, s);
+        case 1: return launch_steps_t<8, 8>(P, gin, gout, gw, mid, mstride, s);
+        default: return launch_steps_t<16, 8>(P, gin, gout, gw, mid, mstride, s);
     }
 }
 
