@@ -682,43 +682,37 @@ int lbm_set_schedule(lbm_ctx* c, int32_t schedule) {
     return fail(c, LBM_E_INVAL, "unknown schedule");
 }
 
+// Steps of the next launch of the context's schedule with n still to go.
+static int next_steps(const lbm_ctx* c, int64_t n) {
+    if (c->schedule != 2) return 1;
+    if (c->steps >= 0 && n >= lbm::kTileSteps) return lbm::kTileSteps;
+    // marching strips; a remainder of one step is left to two two-step launches
+    if (c->march && n >= lbm::kMarchSteps && n != 4) return lbm::kMarchSteps;
+    return n >= 2 ? 2 : 1;
+}
+
+// One launch of next_steps(c, n) steps from state `in` to `out`.
+static hipError_t launch_next(lbm_ctx* c, int64_t n, const double* in, double* out,
+                              hipStream_t s) {
+    const int k = next_steps(c, n);
+    if (c->steps >= 0 && k == lbm::kTileSteps)
+        return lbm::launch_steps(c->kp, c->steps, in, out, c->gw, s);
+    if (k == lbm::kMarchSteps) return lbm::launch_march(c->kp, c->march, in, out, c->gw, s);
+    if (k == 2) return lbm::launch_step2(c->kp, c->tile2, in, out, c->gw, s);
+    return lbm::launch_step(c->kp, c->schedule == 1 ? 1 : 0, c->tile, in, out, c->psi, c->gw, s);
+}
+
 // Launches of `n` steps of the context's schedule from buffer parity `cur`; *cur_out receives the
 // parity holding the result (every launch swaps the buffers).
 static hipError_t enqueue_steps(lbm_ctx* c, int64_t n, int cur, hipStream_t s, int* cur_out) {
-    *cur_out = cur;
-    if (c->schedule == 2 && c->steps >= 0) {
-        for (; n >= lbm::kTileSteps; n -= lbm::kTileSteps) {
-            hipError_t e = lbm::launch_steps(c->kp, c->steps, c->g[cur], c->g[cur ^ 1], c->gw, s);
-            if (e != hipSuccess) return e;
-            cur ^= 1;
-            *cur_out = cur;
-        }
-    }
-    if (c->schedule == 2 && c->march) {
-        // a remainder of one step is left to two two-step launches
-        for (; n >= 3 && n != 4; n -= 3) {
-            hipError_t e = lbm::launch_march(c->kp, c->march, c->g[cur], c->g[cur ^ 1], c->gw, s);
-            if (e != hipSuccess) return e;
-            cur ^= 1;
-            *cur_out = cur;
-        }
-    }
-    if (c->schedule == 2) {
-        for (; n >= 2; n -= 2) {
-            hipError_t e = lbm::launch_step2(c->kp, c->tile2, c->g[cur], c->g[cur ^ 1], c->gw, s);
-            if (e != hipSuccess) return e;
-            cur ^= 1;
-            *cur_out = cur;
-        }
-    }
-    for (int64_t i = 0; i < n; ++i) {
-        hipError_t e = lbm::launch_step(c->kp, c->schedule == 1 ? 1 : 0, c->tile, c->g[cur],
-                                        c->g[cur ^ 1], c->psi, c->gw, s);
-        if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    for (*cur_out = cur; n > 0; n -= next_steps(c, n)) {
+        e = launch_next(c, n, c->g[cur], c->g[cur ^ 1], s);
+        if (e != hipSuccess) break;
         cur ^= 1;
         *cur_out = cur;
     }
-    return hipSuccess;
+    return e;
 }
 
 int lbm_step(lbm_ctx* c, int64_t n) {
@@ -1030,13 +1024,29 @@ int lbm_forward_ckpt(lbm_ctx* c, int64_t nsteps, int32_t K, void* d_adj, size_t 
     c->adj_nsteps = nsteps;
     c->adj_K = K;
     c->adj_ws = d_adj;
-    for (int64_t i = 0; i < nsteps; i += K) {
-        hipError_t e = hipMemcpyAsync(w + A.off_ck + (size_t)(i / K) * A.fbytes, c->g[c->cur], fb,
-                                      hipMemcpyDeviceToDevice, c->stream);
-        if (e != hipSuccess) return hip_fail(c, e, "checkpoint");
-        int rc = lbm_step(c, std::min<int64_t>(K, nsteps - i));
-        if (rc) return rc;
+    (void)hipGetLastError();  // report only errors of this call
+    // The first checkpoint is a copy; every other one is where the last launch of the segment
+    // before writes its state, and where the next segment's first launch reads it (its solid rows
+    // and padding, which no pull reads, stay as they are).
+    auto ck = [&](int64_t j) { return (double*)(w + A.off_ck + (size_t)j * A.fbytes); };
+    hipError_t e = hipMemcpyAsync(ck(0), c->g[c->cur], fb, hipMemcpyDeviceToDevice, c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "checkpoint");
+    int cur = c->cur;  // the buffer that holds the state, -1: a checkpoint
+    const double* in = c->g[cur];
+    for (int64_t j = 0; j < A.nck; ++j) {
+        for (int64_t left = std::min<int64_t>(K, nsteps - j * K); left > 0;) {
+            const int k = next_steps(c, left);
+            const int to = k == left && j + 1 < A.nck ? -1 : (cur == 0 ? 1 : 0);
+            double* out = to < 0 ? ck(j + 1) : c->g[to];
+            e = launch_next(c, left, in, out, c->stream);
+            if (e != hipSuccess) return hip_fail(c, e, "checkpointed forward");
+            in = out;
+            cur = to;
+            left -= k;
+        }
     }
+    c->cur = cur;
+    c->step += nsteps;
     return LBM_OK;
 }
 
@@ -1052,7 +1062,6 @@ int lbm_backward(lbm_ctx* c, int64_t nsteps, int32_t K, void* d_adj, size_t byte
     const KParams& P = c->kp;
     hipStream_t s = c->stream;
     char* w = (char*)d_adj;
-    const size_t fb = (size_t)9 * P.plane * sizeof(double);
     (void)hipGetLastError();  // report only errors of this call
     hipError_t e = lbm::launch_zero(w + A.off_a, A.total - A.off_a, s);
     if (e != hipSuccess) return hip_fail(c, e, "adjoint clear");
@@ -1075,14 +1084,15 @@ int lbm_backward(lbm_ctx* c, int64_t nsteps, int32_t K, void* d_adj, size_t byte
     // its recomputation (ev_rc), and the recomputation of segment j - 2 into the same store waits
     // for the reverse sweep of segment j (ev_free).
     if ((e = adj_streams(c)) != hipSuccess) return hip_fail(c, e, "adjoint stream");
+    // state i of segment j: its checkpoint, or the i-th recomputed state
     auto seg = [&](int64_t j, int64_t i) {
+        if (i == 0) return (double*)(w + A.off_ck + (size_t)j * A.fbytes);
         return (double*)(w + A.off_seg + ((size_t)(j & 1) * K + (size_t)i) * A.fbytes);
     };
     auto seg_len = [&](int64_t j) { return std::min<int64_t>(K, nsteps - j * K); };
     auto recompute = [&](int64_t j) -> hipError_t {
         hipStream_t a = c->aux;
-        hipError_t r = hipMemcpyAsync(seg(j, 0), w + A.off_ck + (size_t)j * A.fbytes, fb,
-                                      hipMemcpyDeviceToDevice, a);
+        hipError_t r = hipSuccess;
         const int64_t len = seg_len(j);
         int64_t i = 0;
         // four or two steps per launch, those before the last written too
@@ -1431,29 +1441,33 @@ int lbm_batch_create_masked(const lbm_params* p, int32_t count, const uint8_t* c
                              out);
 }
 
-// One launch of the ensemble's schedule from buffer parity `cur`, with n steps still to go;
-// *steps receives how many it makes. Schedule 2 makes three by marching strips where those are
-// the better choice (a remainder of one step is left to two two-step launches), else two.
-static hipError_t batch_launch(lbm_batch* b, int64_t n, int cur, int* steps) {
-    if (b->tune.schedule == 2 && b->nsegs && n >= 3 && n != 4) {
-        *steps = lbm::kMarchSteps;
-        return lbm::launch_batch_march(b->geo, b->eos, b->visc, b->d_inst, b->d_segs, b->nsegs, cur,
-                                       b->stream);
-    }
-    if (b->tune.schedule == 2 && n >= 2) {
-        *steps = 2;
+// Steps of the next launch of the ensemble's schedule with n still to go: with schedule 2 three by
+// marching strips where those are the better choice (a remainder of one step is left to two
+// two-step launches), else two.
+static int batch_next_steps(const lbm_batch* b, int64_t n) {
+    if (b->tune.schedule != 2) return 1;
+    if (b->nsegs && n >= lbm::kMarchSteps && n != 4) return lbm::kMarchSteps;
+    return n >= 2 ? 2 : 1;
+}
+
+// One launch of batch_next_steps(b, n) steps from buffer src to dst (see launch_batch_step).
+static hipError_t batch_launch(lbm_batch* b, int64_t n, int src, int dst,
+                               const lbm::Checkpoints* ck = nullptr) {
+    const int k = batch_next_steps(b, n);
+    if (k == lbm::kMarchSteps)
+        return lbm::launch_batch_march(b->geo, b->eos, b->visc, b->d_inst, b->d_segs, b->nsegs, src,
+                                       dst, ck, b->stream);
+    if (k == 2)
         return lbm::launch_batch_step2(b->tune.tile, b->geo, b->eos, b->d_inst, b->d_tile_inst,
-                                       b->ntiles, cur, b->stream);
-    }
-    *steps = 1;
+                                       b->ntiles, src, dst, ck, b->stream);
     return lbm::launch_batch_step(b->tune.tile, b->geo, b->eos, b->d_inst, b->d_tile_inst,
-                                  b->ntiles, cur, b->stream);
+                                  b->ntiles, src, dst, ck, b->stream);
 }
 
 static int batch_direct(lbm_batch* b, int64_t n) {
     while (n > 0) {
-        int k = 0;
-        hipError_t e = batch_launch(b, n, b->cur, &k);
+        const int k = batch_next_steps(b, n);
+        hipError_t e = batch_launch(b, n, b->cur, b->cur ^ 1);
         if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, std::string("batch step: ") + hipGetErrorString(e));
         b->cur ^= 1;
         b->step += k;
@@ -1507,7 +1521,7 @@ int lbm_batch_step(lbm_batch* b, int64_t n) {
             if (e == hipSuccess && (n & 1))
                 e = lbm::launch_batch_step(b->tune.tile, b->geo, b->eos, b->d_inst,
                                            b->d_tile_inst, b->ntiles, cur ^ (npairs & 1),
-                                           b->stream);
+                                           cur ^ (npairs & 1) ^ 1, nullptr, b->stream);
             return e;
         };
         if (!b->pgraph || b->pgraph_n != n || b->pgraph_cur != cur) {
@@ -1532,9 +1546,9 @@ int lbm_batch_step(lbm_batch* b, int64_t n) {
         if (!b->graph[cur]) {
             int rc = capture(b, &b->graph[cur], [&]() {
                 hipError_t e = hipSuccess;
-                for (int left = chunk, c = cur, m = 0; left > 0 && e == hipSuccess; left -= m) {
-                    e = batch_launch(b, left, c, &m);
-                    c ^= 1;
+                for (int left = chunk, c = cur; left > 0 && e == hipSuccess; c ^= 1) {
+                    e = batch_launch(b, left, c, c ^ 1);
+                    left -= batch_next_steps(b, left);
                 }
                 return e;
             });
@@ -1738,17 +1752,50 @@ int lbm_batch_forward_ckpt(lbm_batch* b, int64_t nsteps, int32_t K, void* d_adj,
     b->adj_nsteps = nsteps;
     b->adj_K = K;
     b->adj_ws = d_adj;
-    for (int64_t i = 0; i < nsteps; i += K) {
-        for (int k = 0; k < b->count; ++k) {
-            const size_t fb = (size_t)9 * b->kp[k].plane * sizeof(double);
-            hipError_t e = hipMemcpyAsync(w + L.off[k] + L.A[k].off_ck + (size_t)(i / K) * L.A[k].fbytes,
-                                          b->desc[k].g[b->cur], fb, hipMemcpyDeviceToDevice,
-                                          b->stream);
-            if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "checkpoint");
+    auto copy = [&](int64_t j) {  // checkpoint j of every instance from its current state
+        hipError_t e = hipSuccess;
+        for (int k = 0; k < b->count && e == hipSuccess; ++k)
+            e = hipMemcpyAsync(w + L.off[k] + L.A[k].off_ck + (size_t)j * L.A[k].fbytes,
+                               b->desc[k].g[b->cur], (size_t)9 * b->kp[k].plane * sizeof(double),
+                               hipMemcpyDeviceToDevice, b->stream);
+        return e;
+    };
+    const int64_t nck = (nsteps + K - 1) / K;
+    if (b->tune.schedule == 1 || K >= kGraphChunk || nck > (1 << 30)) {
+        // persistent launches and graph replays work between the ensemble's own buffers
+        for (int64_t j = 0; j < nck; ++j) {
+            if (copy(j) != hipSuccess) return batch_fail(b, LBM_E_HIP, "checkpoint");
+            rc = lbm_batch_step(b, std::min<int64_t>(K, nsteps - j * K));
+            if (rc) return rc;
         }
-        rc = lbm_batch_step(b, std::min<int64_t>(K, nsteps - i));
-        if (rc) return rc;
+        return LBM_OK;
     }
+    // The first checkpoint is a copy; every other one is where the last launch of the segment
+    // before writes its state, and where the next segment's first launch reads it. The table of
+    // their addresses lies in the adjoint workspace, in the place of the reverse sweep's.
+    std::vector<lbm::Checkpoints> ck(b->count);
+    for (int k = 0; k < b->count; ++k)
+        ck[k] = {(double*)(w + L.off[k] + L.A[k].off_ck),
+                 (long long)(L.A[k].fbytes / sizeof(double))};
+    const lbm::Checkpoints* d_ck = (const lbm::Checkpoints*)(w + L.off_inst);
+    static_assert(sizeof(lbm::Checkpoints) <= sizeof(lbm::AdjInst), "the table fits");
+    hipError_t e = host_copy(b->stream, w + L.off_inst, ck.data(),
+                             ck.size() * sizeof(lbm::Checkpoints), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = copy(0);
+    if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "checkpoint");
+    int src = b->cur;
+    for (int64_t j = 0; j < nck; ++j) {
+        for (int64_t left = std::min<int64_t>(K, nsteps - j * K); left > 0;) {
+            const int k = batch_next_steps(b, left);
+            const int dst = k == left && j + 1 < nck ? (int)(2 + j + 1) : (src == 0 ? 1 : 0);
+            e = batch_launch(b, left, src, dst, d_ck);
+            if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "checkpointed forward");
+            src = dst;
+            left -= k;
+        }
+    }
+    b->cur = src;
+    b->step += nsteps;
     return LBM_OK;
 }
 
@@ -1801,6 +1848,7 @@ int lbm_batch_backward(lbm_batch* b, int64_t nsteps, int32_t K, void* d_adj, siz
         lbm::AdjInst& d = inst[i];
         d = lbm::AdjInst{};
         d.P = b->kp[i];
+        d.ck = (double*)(base + A.off_ck);
         d.seg = (double*)(base + A.off_seg);
         d.fstride = (long long)(A.fbytes / sizeof(double));
         for (int k = 0; k < 2; ++k) {
@@ -1849,16 +1897,13 @@ int lbm_batch_backward(lbm_batch* b, int64_t nsteps, int32_t K, void* d_adj, siz
     int k = 0;  // buffers of the later step
     for (int64_t j = nck - 1; j >= 0; --j) {
         const int64_t len = std::min<int64_t>(K, nsteps - j * K);
-        for (int i = 0; i < b->count && e == hipSuccess; ++i)
-            e = hipMemcpyAsync(inst[i].seg, w + L.off[i] + L.A[i].off_ck + (size_t)j * L.A[i].fbytes,
-                               (size_t)9 * b->kp[i].plane * sizeof(double), hipMemcpyDeviceToDevice, s);
         int64_t i = 0;
         for (; i + 2 <= len - 1 && e == hipSuccess; i += 2)
-            e = lbm::launch_batch_seg_step2(b->eos, d_inst, d_tiles8, L.ntiles8, (int)i, s);
+            e = lbm::launch_batch_seg_step2(b->eos, d_inst, d_tiles8, L.ntiles8, (int)i, (int)j, s);
         if (i + 1 <= len - 1 && e == hipSuccess)
-            e = lbm::launch_batch_seg_step(b->eos, d_inst, d_tiles, L.ntiles, (int)i, s);
+            e = lbm::launch_batch_seg_step(b->eos, d_inst, d_tiles, L.ntiles, (int)i, (int)j, s);
         for (i = len - 1; i >= 0 && e == hipSuccess; --i) {
-            e = lbm::launch_batch_adj(b->eos, d_inst, d_tiles, L.ntiles, (int)i, k, s);
+            e = lbm::launch_batch_adj(b->eos, d_inst, d_tiles, L.ntiles, (int)i, (int)j, k, s);
             k ^= 1;
         }
         if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "ensemble adjoint segment");

@@ -29,6 +29,13 @@ __device__ __forceinline__ T* gptr(T* p) {
     return (T*)(__attribute__((address_space(1))) T*)(unsigned long long)p;
 }
 
+// Buffer `b` of an instance: its population buffer 0 or 1, or from 2 on the checkpoints of an
+// adjoint run.
+__device__ __forceinline__ double* inst_buffer(const InstDesc* D, const Checkpoints* ck, int i,
+                                               int b) {
+    return b < 2 ? gptr(D->g[b]) : gptr(ck[i].base) + (long long)(b - 2) * ck[i].stride;
+}
+
 __device__ __forceinline__ void batch_tile_origin(const InstDesc* D, int t, int TX, int TY,
                                                   int& x0, int& y0) {
     const int lt = t - D->tile0;
@@ -42,13 +49,15 @@ __device__ __forceinline__ void batch_tile_origin(const InstDesc* D, int t, int 
 template <int TX, int TY, int GEO, int EOS>
 __global__ __launch_bounds__(TX* TY) void k_batch_step(const InstDesc* __restrict__ inst,
                                                        const int* __restrict__ tile_inst,
-                                                       int ntiles, int cur) {
+                                                       int ntiles, int src, int dst,
+                                                       const Checkpoints* __restrict__ ck) {
     __shared__ double sp[(TY + 2) * (TX + 2)];
-    const int t = xcd_tile(blockIdx.x, ntiles);
-    const InstDesc* D = inst + tile_inst[t];
+    const int t = xcd_tile(blockIdx.x, ntiles), n = tile_inst[t];
+    const InstDesc* D = inst + n;
     int x0, y0;
     batch_tile_origin(D, t, TX, TY, x0, y0);
-    step_tile<TX, TY, true, GEO, EOS>(D->P, D->g[cur], D->g[cur ^ 1], nullptr, D->gw, x0, y0, sp);
+    step_tile<TX, TY, true, GEO, EOS>(D->P, inst_buffer(D, ck, n, src), inst_buffer(D, ck, n, dst),
+                                      nullptr, D->gw, x0, y0, sp);
 }
 
 // Two steps per launch over the work-list (the tiles are the output tiles of step2_tile), NTH
@@ -57,27 +66,31 @@ template <int TX, int TY, int GEO, int EOS, int NTH = step2_threads(TX, TY, GEO)
 __global__ __launch_bounds__(NTH, NTH == step2_threads(TX, TY, GEO) ? step2_waves(TX, TY, GEO)
                                                                     : (NTH / 64 + 3) / 4) void
 k_batch_step2(
-    const InstDesc* __restrict__ inst, const int* __restrict__ tile_inst, int ntiles, int cur) {
+    const InstDesc* __restrict__ inst, const int* __restrict__ tile_inst, int ntiles, int src,
+    int dst, const Checkpoints* __restrict__ ck) {
     __shared__ Step2Lds<TX, TY, GEO> lds;
-    const int t = xcd_tile(blockIdx.x, ntiles);
-    const InstDesc* D = inst + tile_inst[t];
+    const int t = xcd_tile(blockIdx.x, ntiles), n = tile_inst[t];
+    const InstDesc* D = inst + n;
     int x0, y0;
     batch_tile_origin(D, t, TX, TY, x0, y0);
-    step2_tile_any<TX, TY, GEO, EOS, false, false, NTH>(D->P, gptr(D->g[cur]), gptr(D->g[cur ^ 1]),
-                                                        gptr(D->gw), x0, y0, lds);
+    step2_tile_any<TX, TY, GEO, EOS, false, false, NTH>(D->P, inst_buffer(D, ck, n, src),
+                                                        inst_buffer(D, ck, n, dst), gptr(D->gw),
+                                                        x0, y0, lds);
 }
 
 // kMarchSteps steps per launch over the ensemble's list of segments, one per wave (march_strip).
 template <int GEO, int EOS, int VISC>
 __global__ __launch_bounds__(64 * kMarchWaves, 2) void k_batch_march(
-    const InstDesc* __restrict__ inst, const MarchSeg* __restrict__ segs, int n, int cur) {
+    const InstDesc* __restrict__ inst, const MarchSeg* __restrict__ segs, int n, int src, int dst,
+    const Checkpoints* __restrict__ ck) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int w = xcd_tile(blockIdx.x, gridDim.x) * kMarchWaves + wave;
     if (w >= n) return;
     const MarchSeg S = segs[w];
     const InstDesc* D = inst + S.inst;
     const KParams P = D->P;
-    march_strip<kMarchSteps, GEO, EOS, VISC, DppLane>(P, gptr(D->g[cur]), gptr(D->g[cur ^ 1]),
+    march_strip<kMarchSteps, GEO, EOS, VISC, DppLane>(P, inst_buffer(D, ck, S.inst, src),
+                                                      inst_buffer(D, ck, S.inst, dst),
                                                       gptr(D->gw), S.x0, S.y0, S.y1,
                                                       threadIdx.x & 63);
 }
@@ -314,49 +327,52 @@ __device__ __forceinline__ void adj_tile_origin(const AdjInst* D, int t, int& x0
     y0 = D->P.y_lo + (lt / D->ntx) * 4;
 }
 
+// State i of segment j: the checkpoint itself, or the i-th recomputed state.
+__device__ __forceinline__ double* seg_state(const AdjInst* D, int i, int j) {
+    return i ? gptr(D->seg) + (long long)i * D->fstride : gptr(D->ck) + (long long)j * D->fstride;
+}
+
 // Segment states i -> i+1, i+2 of every instance (two steps per launch, the first written too),
 // over a work-list of 64 x 8 output tiles (the recomputation work-list).
 template <int EOS>
 __global__ __launch_bounds__(step2_threads(64, 8, GEO_ROWS), step2_waves(64, 8, GEO_ROWS)) void
 k_batch_seg_step2(const AdjInst* __restrict__ inst, const int* __restrict__ tile_inst, int ntiles,
-                  int i) {
+                  int i, int j) {
     __shared__ Step2Lds<64, 8, GEO_ROWS> lds;
     const int t = xcd_tile(blockIdx.x, ntiles);
     const AdjInst* D = inst + tile_inst[t];
     const int lt = t - D->tile0_8;
     const int x0 = (lt % D->ntx) * 64;
     const int y0 = D->P.y_lo + (lt / D->ntx) * 8;
-    double* s0 = gptr(D->seg) + (long long)i * D->fstride;
-    step2_tile_any<64, 8, GEO_ROWS, EOS, true>(D->P, s0, s0 + 2 * D->fstride, gptr(D->gw), x0, y0,
-                                               lds, s0 + D->fstride);
+    step2_tile_any<64, 8, GEO_ROWS, EOS, true>(D->P, seg_state(D, i, j), seg_state(D, i + 2, j),
+                                               gptr(D->gw), x0, y0, lds, seg_state(D, i + 1, j));
 }
 
 // Segment state i -> i+1 of every instance (one fused step).
 template <int EOS>
 __global__ __launch_bounds__(256) void k_batch_seg_step(const AdjInst* __restrict__ inst,
                                                         const int* __restrict__ tile_inst,
-                                                        int ntiles, int i) {
+                                                        int ntiles, int i, int j) {
     __shared__ double sp[6 * 66];
     const int t = xcd_tile(blockIdx.x, ntiles);
     const AdjInst* D = inst + tile_inst[t];
     int x0, y0;
     adj_tile_origin(D, t, x0, y0);
-    double* s0 = gptr(D->seg) + (long long)i * D->fstride;
-    step_tile<64, 4, true, GEO_ROWS, EOS>(D->P, s0, s0 + D->fstride, nullptr, gptr(D->gw), x0, y0,
-                                          sp);
+    step_tile<64, 4, true, GEO_ROWS, EOS>(D->P, seg_state(D, i, j), seg_state(D, i + 1, j), nullptr,
+                                          gptr(D->gw), x0, y0, sp);
 }
 
-// One reverse step of every instance: segment state i, later-step buffers of parity k.
+// One reverse step of every instance: state i of segment j, later-step buffers of parity k.
 template <int EOS>
 __global__ __launch_bounds__(256) void k_batch_adj(const AdjInst* __restrict__ inst,
                                                    const int* __restrict__ tile_inst, int ntiles,
-                                                   int i, int k) {
+                                                   int i, int j, int k) {
     __shared__ AdjLds<64, 4> lds;
     const int t = xcd_tile(blockIdx.x, ntiles);
     const AdjInst* D = inst + tile_inst[t];
     int x0, y0;
     adj_tile_origin(D, t, x0, y0);
-    const AdjPtrs A{gptr(D->seg) + (long long)i * D->fstride,
+    const AdjPtrs A{seg_state(D, i, j),
                     gptr(D->a[k]),     gptr(D->q[k]),     gptr(D->p0[k]),     gptr(D->dpsi[k]),
                     gptr(D->rv[k]),    gptr(D->gw),       gptr(D->a[k ^ 1]),  gptr(D->q[k ^ 1]),
                     gptr(D->p0[k ^ 1]), gptr(D->dpsi[k ^ 1]), gptr(D->rv[k ^ 1]), gptr(D->gg)};
@@ -400,10 +416,11 @@ static hipError_t dispatch(int geo, int eos, F&& f) {
 
 template <int TX, int TY>
 static hipError_t launch_batch_t(int geo, int eos, const InstDesc* inst, const int* tile_inst,
-                                 int ntiles, int cur, hipStream_t s) {
+                                 int ntiles, int src,
+                                 int dst, const Checkpoints* ck, hipStream_t s) {
     return dispatch(geo, eos, [&](auto g, auto e) {
         hipLaunchKernelGGL((k_batch_step<TX, TY, decltype(g)::value, decltype(e)::value>),
-                           dim3(ntiles), dim3(TX * TY), 0, s, inst, tile_inst, ntiles, cur);
+                           dim3(ntiles), dim3(TX * TY), 0, s, inst, tile_inst, ntiles, src, dst, ck);
         return hipGetLastError();
     });
 }
@@ -449,13 +466,14 @@ int batch_tiles(int tile) { return tile >= 0 && tile < 4; }
 
 template <int TX, int TY>
 static hipError_t launch_batch2_t(int geo, int eos, const InstDesc* inst, const int* tile_inst,
-                                  int ntiles, int cur, hipStream_t s) {
+                                  int ntiles, int src,
+                                 int dst, const Checkpoints* ck, hipStream_t s) {
     return dispatch(geo, eos, [&](auto g, auto e) {
         constexpr int G = decltype(g)::value;
         constexpr int NT = TX == 32 && TY == 4 ? step2_wide_threads(32, 4)
                                                : step2_threads(TX, TY, G);
         hipLaunchKernelGGL((k_batch_step2<TX, TY, G, decltype(e)::value, NT>), dim3(ntiles),
-                           dim3(NT), 0, s, inst, tile_inst, ntiles, cur);
+                           dim3(NT), 0, s, inst, tile_inst, ntiles, src, dst, ck);
         return hipGetLastError();
     });
 }
@@ -471,24 +489,26 @@ void batch_tile_shape(int tile, int* tx, int* ty) {
 
 // Two steps per launch (schedule 2) with the output tiles of the work-list's tile shape.
 hipError_t launch_batch_step2(int tile, int geo, int eos, const InstDesc* inst,
-                              const int* tile_inst, int ntiles, int cur, hipStream_t s) {
+                              const int* tile_inst, int ntiles, int src, int dst,
+                              const Checkpoints* ck, hipStream_t s) {
     switch (tile) {
-        case 4: return launch_batch2_t<32, 4>(geo, eos, inst, tile_inst, ntiles, cur, s);
-        case 1: return launch_batch2_t<64, 8>(geo, eos, inst, tile_inst, ntiles, cur, s);
-        case 2: return launch_batch2_t<64, 16>(geo, eos, inst, tile_inst, ntiles, cur, s);
-        case 3: return launch_batch2_t<128, 4>(geo, eos, inst, tile_inst, ntiles, cur, s);
-        default: return launch_batch2_t<64, 4>(geo, eos, inst, tile_inst, ntiles, cur, s);
+        case 4: return launch_batch2_t<32, 4>(geo, eos, inst, tile_inst, ntiles, src, dst, ck, s);
+        case 1: return launch_batch2_t<64, 8>(geo, eos, inst, tile_inst, ntiles, src, dst, ck, s);
+        case 2: return launch_batch2_t<64, 16>(geo, eos, inst, tile_inst, ntiles, src, dst, ck, s);
+        case 3: return launch_batch2_t<128, 4>(geo, eos, inst, tile_inst, ntiles, src, dst, ck, s);
+        default: return launch_batch2_t<64, 4>(geo, eos, inst, tile_inst, ntiles, src, dst, ck, s);
     }
 }
 
 hipError_t launch_batch_step(int tile, int geo, int eos, const InstDesc* inst,
-                             const int* tile_inst, int ntiles, int cur, hipStream_t s) {
+                             const int* tile_inst, int ntiles, int src, int dst,
+                              const Checkpoints* ck, hipStream_t s) {
     switch (tile) {
-        case 4: return launch_batch_t<32, 4>(geo, eos, inst, tile_inst, ntiles, cur, s);
-        case 1: return launch_batch_t<64, 8>(geo, eos, inst, tile_inst, ntiles, cur, s);
-        case 2: return launch_batch_t<64, 16>(geo, eos, inst, tile_inst, ntiles, cur, s);
-        case 3: return launch_batch_t<128, 4>(geo, eos, inst, tile_inst, ntiles, cur, s);
-        default: return launch_batch_t<64, 4>(geo, eos, inst, tile_inst, ntiles, cur, s);
+        case 4: return launch_batch_t<32, 4>(geo, eos, inst, tile_inst, ntiles, src, dst, ck, s);
+        case 1: return launch_batch_t<64, 8>(geo, eos, inst, tile_inst, ntiles, src, dst, ck, s);
+        case 2: return launch_batch_t<64, 16>(geo, eos, inst, tile_inst, ntiles, src, dst, ck, s);
+        case 3: return launch_batch_t<128, 4>(geo, eos, inst, tile_inst, ntiles, src, dst, ck, s);
+        default: return launch_batch_t<64, 4>(geo, eos, inst, tile_inst, ntiles, src, dst, ck, s);
     }
 }
 
@@ -528,28 +548,28 @@ static hipError_t with_eos(int eos, F&& f) {
 }
 
 hipError_t launch_batch_seg_step2(int eos, const AdjInst* inst, const int* tile_inst, int ntiles,
-                                  int i, hipStream_t s) {
+                                  int i, int j, hipStream_t s) {
     return with_eos(eos, [&](auto e) {
         hipLaunchKernelGGL((k_batch_seg_step2<decltype(e)::value>), dim3(ntiles),
-                           dim3(step2_threads(64, 8, GEO_ROWS)), 0, s, inst, tile_inst, ntiles, i);
+                           dim3(step2_threads(64, 8, GEO_ROWS)), 0, s, inst, tile_inst, ntiles, i, j);
         return hipGetLastError();
     });
 }
 
 hipError_t launch_batch_seg_step(int eos, const AdjInst* inst, const int* tile_inst, int ntiles,
-                                 int i, hipStream_t s) {
+                                 int i, int j, hipStream_t s) {
     return with_eos(eos, [&](auto e) {
         hipLaunchKernelGGL((k_batch_seg_step<decltype(e)::value>), dim3(ntiles), dim3(256), 0, s,
-                           inst, tile_inst, ntiles, i);
+                           inst, tile_inst, ntiles, i, j);
         return hipGetLastError();
     });
 }
 
 hipError_t launch_batch_adj(int eos, const AdjInst* inst, const int* tile_inst, int ntiles, int i,
-                            int k, hipStream_t s) {
+                            int j, int k, hipStream_t s) {
     return with_eos(eos, [&](auto e) {
         hipLaunchKernelGGL((k_batch_adj<decltype(e)::value>), dim3(ntiles), dim3(256), 0, s, inst,
-                           tile_inst, ntiles, i, k);
+                           tile_inst, ntiles, i, j, k);
         return hipGetLastError();
     });
 }
@@ -562,7 +582,8 @@ hipError_t launch_batch_adj_gw(const AdjInst* inst, int count, int max_nx, int k
 }
 
 hipError_t launch_batch_march(int geo, int eos, int visc, const InstDesc* inst,
-                              const MarchSeg* segs, int n, int cur, hipStream_t s) {
+                              const MarchSeg* segs, int n, int src, int dst,
+                              const Checkpoints* ck, hipStream_t s) {
     return dispatch(geo, eos, [&](auto g, auto e) {
         constexpr int G = decltype(g)::value, E = decltype(e)::value;
         if constexpr (G == GEO_MASK) {
@@ -571,7 +592,7 @@ hipError_t launch_batch_march(int geo, int eos, int visc, const InstDesc* inst,
             auto go = [&](auto v) {
                 hipLaunchKernelGGL((k_batch_march<G, E, decltype(v)::value>),
                                    dim3((n + kMarchWaves - 1) / kMarchWaves),
-                                   dim3(64 * kMarchWaves), 0, s, inst, segs, n, cur);
+                                   dim3(64 * kMarchWaves), 0, s, inst, segs, n, src, dst, ck);
                 return hipGetLastError();
             };
             if (visc == 1) return go(std::integral_constant<int, 1>{});

@@ -21,11 +21,18 @@ struct InstDesc {
     int pad;
 };
 
+// Checkpoints of one instance of an ensemble's adjoint run (device memory).
+struct Checkpoints {
+    double* base;
+    long long stride;  // doubles between consecutive states
+};
+
 // One instance of an ensemble's adjoint run (device memory): its segment of recomputed states
 // and the adjoint quantities of two consecutive reverse steps (see AdjPtrs).
 struct AdjInst {
     KParams P;
-    double* seg;       // the segment's states, fstride doubles apart
+    double* ck;        // checkpoints (state 0 of every segment), fstride doubles apart
+    double* seg;       // the segment's recomputed states (from state 1), fstride doubles apart
     long long fstride;
     double* a[2];
     double* q[2];
@@ -68,7 +75,8 @@ hipError_t launch_march(const KParams& P, int h, const double* gin, double* gout
                         hipStream_t s);
 // visc: 1 every instance has one viscosity, 2 none has, 0 some have
 hipError_t launch_batch_march(int geo, int eos, int visc, const InstDesc* inst,
-                              const MarchSeg* segs, int n, int cur, hipStream_t s);
+                              const MarchSeg* segs, int n, int src, int dst,
+                              const Checkpoints* ck, hipStream_t s);
 // Multi-step tiles (lbm_steps.h): kTileSteps steps per launch on lattices too small to fill the GPU.
 constexpr int kTileSteps = 4;
 // Tile of a lattice of nx columns and `rows` fluid rows (for launch_steps), or -1 where the
@@ -123,11 +131,14 @@ hipError_t launch_loss_seed(const KParams& P, double w_c, double w_w, double yc,
 int batch_tiles(int tile);
 // geo: GEO_ROWS, GEO_WET (some instance uses the wet-node wall) or GEO_MASK (every instance has
 // a solid mask); eos: EOS_CS or EOS_PW when every instance uses it, else EOS_ANY. They select the
-// kernels compiled for that variant.
+// kernels compiled for that variant. src, dst: the buffers read and written, 0 or 1 of the instances'
+// own, or 2 + j for checkpoint j of an adjoint run (ck: one entry per instance, else null).
 hipError_t launch_batch_step(int tile, int geo, int eos, const InstDesc* inst,
-                             const int* tile_inst, int ntiles, int cur, hipStream_t s);
+                             const int* tile_inst, int ntiles, int src, int dst,
+                             const Checkpoints* ck, hipStream_t s);
 hipError_t launch_batch_step2(int tile, int geo, int eos, const InstDesc* inst,
-                              const int* tile_inst, int ntiles, int cur, hipStream_t s);
+                              const int* tile_inst, int ntiles, int src, int dst,
+                              const Checkpoints* ck, hipStream_t s);
 // The persistent schedule's control block (kControlWords 8-byte words of the ensemble
 // workspace): the grid barrier's arrival counter (word 0), the abort flag (an int at byte 64),
 // and per XCD a tile-ticket counter, a barrier arrival counter, a barrier gate and a count of
@@ -152,15 +163,15 @@ hipError_t launch_batch_obs(const InstDesc* inst, int count, int max_blocks, con
                             int cur, double* out, hipStream_t s);
 int batch_persistent_occupancy(int tile);
 // ensemble adjoint, over work-lists of the tiles of every instance (bounce-back walls):
-// recomputation of segment states i -> i+1, i+2 (two steps, 64 x 8 output tiles) or i -> i+1 (one
-// step, 64 x 4), one reverse step of segment state i (64 x 4; k: parity of the later step's
+// recomputation of states i -> i+1, i+2 of segment j (two steps, 64 x 8 output tiles) or i -> i+1 (one
+// step, 64 x 4), one reverse step of its state i (64 x 4; k: parity of the later step's
 // buffers), and the last step's G_w gradient
 hipError_t launch_batch_seg_step2(int eos, const AdjInst* inst, const int* tile_inst, int ntiles,
-                                  int i, hipStream_t s);
+                                  int i, int j, hipStream_t s);
 hipError_t launch_batch_seg_step(int eos, const AdjInst* inst, const int* tile_inst, int ntiles,
-                                 int i, hipStream_t s);
+                                 int i, int j, hipStream_t s);
 hipError_t launch_batch_adj(int eos, const AdjInst* inst, const int* tile_inst, int ntiles, int i,
-                            int k, hipStream_t s);
+                            int j, int k, hipStream_t s);
 hipError_t launch_batch_adj_gw(const AdjInst* inst, int count, int max_nx, int k,
                                hipStream_t s);
 
