@@ -9,6 +9,7 @@
 // the reverse mode of the MRT collision (a^{n-1}, q = dL/ds, p0 = dL/dpsi as the node's own
 // pre-factor, psi', and r = dL/dA on the wall rows). dL/dG_w accumulates on the solid nodes of
 // both walls from each step's r, the last step's by k_adj_gw.
+#include "lbm_adj2.h"
 #include "lbm_device.h"
 #include "lbm_internal.h"
 
@@ -21,6 +22,16 @@ __global__ __launch_bounds__(NTH) void k_adj(KParams P, AdjPtrs A) {
     const int nty = (P.y_hi - P.y_lo + TY) / TY;
     const int tile = xcd_tile(blockIdx.x, ntx * nty);
     adj_tile<TX, TY, NTH, EOS>(P, A, (tile % ntx) * TX, P.y_lo + (tile / ntx) * TY, lds);
+}
+
+// Two reverse steps (adj2_tile).
+template <int EOS>
+__global__ __launch_bounds__(kAdj2Threads) void k_adj2(KParams P, Adj2Ptrs B) {
+    __shared__ Adj2Lds lds;
+    const int ntx = (P.nx + kAdj2X - 1) / kAdj2X;
+    const int nty = (P.y_hi - P.y_lo + kAdj2Y) / kAdj2Y;
+    const int tile = xcd_tile(blockIdx.x, ntx * nty);
+    adj2_tile<EOS>(P, B, (tile % ntx) * kAdj2X, P.y_lo + (tile / ntx) * kAdj2Y, lds);
 }
 
 // dL/dG_w of the wall vectors of the last reverse step.
@@ -120,6 +131,21 @@ hipError_t launch_adj(const KParams& P, const AdjPtrs& A, hipStream_t s) {
     const int tiles64 = ((P.nx + 63) / 64) * ((P.y_hi - P.y_lo + 4) / 4);
     if (tiles64 < 512) return launch_adj_t<32, 4, 256>(P, A, s);
     return launch_adj_t<64, 4, 256>(P, A, s);
+}
+
+bool adj2_fits(const KParams& P) {
+    return (long long)((P.nx + kAdj2X - 1) / kAdj2X) * ((P.y_hi - P.y_lo + kAdj2Y) / kAdj2Y) <= 512;
+}
+
+hipError_t launch_adj2(const KParams& P, const AdjPtrs& A, const double* gprev2, hipStream_t s) {
+    const int ntx = (P.nx + kAdj2X - 1) / kAdj2X;
+    const int nty = (P.y_hi - P.y_lo + kAdj2Y) / kAdj2Y;
+    const Adj2Ptrs B{A, gprev2};
+    if (P.eos == 0)
+        hipLaunchKernelGGL((k_adj2<EOS_CS>), dim3(ntx * nty), dim3(kAdj2Threads), 0, s, P, B);
+    else
+        hipLaunchKernelGGL((k_adj2<EOS_PW>), dim3(ntx * nty), dim3(kAdj2Threads), 0, s, P, B);
+    return hipGetLastError();
 }
 
 hipError_t launch_adj_gw(const KParams& P, const double* rv, double* gwgrad, hipStream_t s) {

@@ -1111,6 +1111,7 @@ int lbm_backward(lbm_ctx* c, int64_t nsteps, int32_t K, void* d_adj, size_t byte
     if (e == hipSuccess) e = hipStreamWaitEvent(c->aux, c->ev_start, 0);
     if (e == hipSuccess) e = recompute(A.nck - 1);
     if (e != hipSuccess) return hip_fail(c, e, "segment recompute");
+    const bool two = lbm::adj2_fits(P);
     int k = 0;  // buffers of the later step
     for (int64_t j = A.nck - 1; j >= 0; --j) {
         if (j >= 1) {
@@ -1121,12 +1122,13 @@ int lbm_backward(lbm_ctx* c, int64_t nsteps, int32_t K, void* d_adj, size_t byte
         }
         e = hipStreamWaitEvent(s, c->ev_rc[j & 1], 0);
         if (e != hipSuccess) return hip_fail(c, e, "segment wait");
-        // the segment's adjoint steps in reverse
+        // the segment's adjoint steps in reverse, two per launch on small lattices
         for (int64_t i = seg_len(j) - 1; i >= 0; --i) {
             lbm::AdjPtrs ap{seg(j, i),    a_buf[k],     q_buf[k],     p0_buf[k],
                             dpsi_buf[k],  rv_buf[k],    c->gw,        a_buf[k ^ 1],
                             q_buf[k ^ 1], p0_buf[k ^ 1], dpsi_buf[k ^ 1], rv_buf[k ^ 1], gg};
-            e = lbm::launch_adj(P, ap, s);
+            if (two && i >= 1) e = lbm::launch_adj2(P, ap, seg(j, --i), s);
+            else e = lbm::launch_adj(P, ap, s);
             if (e != hipSuccess) return hip_fail(c, e, "adjoint step");
             k ^= 1;
         }

@@ -1435,24 +1435,32 @@ struct AdjLds {
 };
 
 // dL/dG_w of the solid node below (bottom wall) or above (top wall) fluid node x of a wall row,
-// from the wall vectors r = dL/dA of one step (omega = w/3: 1/9 axial, 1/36 diagonal).
-__device__ __forceinline__ void adj_gw_node(const KParams& P, const double* __restrict__ rv,
-                                            double* __restrict__ gwgrad, int x, int y) {
+// from the wall vectors r = dL/dA of one step (omega = w/3: 1/9 axial, 1/36 diagonal): four rows rv
+// (bottom x, y; top x, y), `row` apart, with the node and its neighbours at m, i, p.
+__device__ __forceinline__ void adj_gw_sum(const KParams& P, const double* __restrict__ rv, int row,
+                                           unsigned m, unsigned i, unsigned p,
+                                           double* __restrict__ gwgrad, int x, int y) {
 #pragma clang fp contract(off)
-    const unsigned pitch = P.pitch, ux = x;
-    const unsigned xm = ux == 0 ? P.nx - 1 : ux - 1;
-    const unsigned xp = ux == (unsigned)P.nx - 1 ? 0 : ux + 1;
     if (y == 1) {
         const double* rX = rv;
-        const double* rY = rv + pitch;
-        gwgrad[ux] += -rY[ux] * (1.0 / 9.0) + ((-rX[xp] - rY[xp]) + (rX[xm] - rY[xm])) * (1.0 / 36.0);
+        const double* rY = rv + row;
+        gwgrad[x] += -rY[i] * (1.0 / 9.0) + ((-rX[p] - rY[p]) + (rX[m] - rY[m])) * (1.0 / 36.0);
     }
     if (y == P.ny - 2) {
-        const double* rX = rv + 2 * pitch;
-        const double* rY = rv + 3 * pitch;
-        gwgrad[pitch + ux] +=
-            rY[ux] * (1.0 / 9.0) + ((rX[xm] + rY[xm]) + (rY[xp] - rX[xp])) * (1.0 / 36.0);
+        const double* rX = rv + 2 * row;
+        const double* rY = rv + 3 * row;
+        gwgrad[P.pitch + x] +=
+            rY[i] * (1.0 / 9.0) + ((rX[m] + rY[m]) + (rY[p] - rX[p])) * (1.0 / 36.0);
     }
+}
+
+// adj_gw_sum from wall vectors in memory (rows of the lattice's pitch).
+__device__ __forceinline__ void adj_gw_node(const KParams& P, const double* __restrict__ rv,
+                                            double* __restrict__ gwgrad, int x, int y) {
+    const unsigned ux = x;
+    const unsigned xm = ux == 0 ? P.nx - 1 : ux - 1;
+    const unsigned xp = ux == (unsigned)P.nx - 1 ? 0 : ux + 1;
+    adj_gw_sum(P, rv, P.pitch, xm, ux, xp, gwgrad, x, y);
 }
 
 // One reverse step on a TX x TY tile (bounce-back or periodic rows), executed by TX * TY threads:

@@ -120,6 +120,9 @@ hipError_t launch_obs(const KParams& P, const double* gin, const double* gw, con
 
 // adjoint
 hipError_t launch_adj(const KParams& P, const AdjPtrs& A, hipStream_t s);
+// Two reverse steps (lbm_adj2.h) where adj2_fits: of A's forward state, then of gprev2.
+bool adj2_fits(const KParams& P);
+hipError_t launch_adj2(const KParams& P, const AdjPtrs& A, const double* gprev2, hipStream_t s);
 hipError_t launch_adj_gw(const KParams& P, const double* rv, double* gwgrad, hipStream_t s);
 int loss_blocks(const KParams& P);
 hipError_t launch_loss(const KParams& P, const double* g, double* part, double* out,
