@@ -387,8 +387,8 @@ static int strips_of(const MarchShape& m) {
 // (2048 x 1024: 26 segments of 40 rows, 988 waves, 96 us per launch; 52 of 20, 1976 waves, 92 us;
 // 32 of 32, 1216 waves, 116 us). The two-step tiles make 49 updates per ns on a full chip. The
 // line lies near a million nodes: 1024 x 512 takes 11.3 us per step with tiles and 14.3 marching,
-// 1400 x 700 19.2 and 18.3, 1500 x 1001 27.7 and 24.0, 2048 x 1024 39.4 and 30.7, 4096 x 4096
-// 312 and 215.
+// 1400 x 700 19.2 and 16.7, 1500 x 1001 27.7 and 23.2, 2048 x 1024 39.4 and 29.6, 4096 x 4096
+// 312 and 212.
 int march_rows(const MarchShape* m, int count) {
     constexpr int H = 2 * kMarchSteps - 1;
     int rmax = 0;

@@ -117,10 +117,11 @@ __device__ __forceinline__ void march_strip(const KParams& P, const double* __re
         L[t].F[0] = L[t].F[1] = 0.0;
     }
     const int first = rows && y0 - H < 1 ? 1 : y0 - H, last = y1 + H;
-    // One row of every level. f: the pulled populations of row i at level 0. PLAIN: every level
-    // is in use and no row of this pass lies next to a wall (no condition is left).
-    auto row = [&](auto plain, int i, double f[9]) {
-        constexpr bool PLAIN = decltype(plain)::value;
+    // One row of every level. f: the pulled populations of row i at level 0. WALL: some row of this
+    // pass may lie next to a wall (or, with periodic rows, be stored past the seam); PART: some
+    // levels may not be in use yet. A pass with neither has no condition left.
+    auto row = [&](auto wall, auto part, int i, double f[9]) {
+        constexpr bool WALL = decltype(wall)::value, PART = decltype(part)::value;
 #pragma unroll
         for (int t = 0; t < T; ++t) {
             MarchLevel& M = L[t];
@@ -131,14 +132,14 @@ __device__ __forceinline__ void march_strip(const KParams& P, const double* __re
                 lo = lo < 1 ? 1 : lo;
                 hi = hi > top ? top : hi;
             }
-            if (!PLAIN && (p < lo - 1 || (rows && p < 1))) break;  // nothing is here yet
+            if (PART && (p < lo - 1 || (WALL && rows && p < 1))) break;  // nothing is here yet
             double n[3], rho = 1.0;
-            if (PLAIN || !rows || p <= top) {
+            if (!WALL || !rows || p <= top) {
                 rho = sum9(f);
                 n[1] = psi_of_rho<EOS>(P, rho);
                 n[0] = X::left(n[1]);
                 n[2] = X::right(n[1]);
-                if (!PLAIN && rows && p == 1) {  // the solid row below has this row's psi, or none
+                if (WALL && rows && p == 1) {  // the solid row below has this row's psi, or none
 #pragma unroll
                     for (int k = 0; k < 3; ++k) M.w1[k] = P.ghost ? n[k] : 0.0;
                 }
@@ -147,12 +148,12 @@ __device__ __forceinline__ void march_strip(const KParams& P, const double* __re
                 for (int k = 0; k < 3; ++k) n[k] = P.ghost ? M.w1[k] : 0.0;
             }
             double s[9];  // f* of row c
-            if (PLAIN || (c >= lo && c <= hi)) {
+            if ((!PART || c >= lo) && (!WALL || c <= hi)) {
 #pragma unroll
                 for (int k = 0; k < 9; ++k) s[k] = M.f[k];
                 double sx, sy;
                 cohesion_sum(M.w0[0], M.w0[1], M.w0[2], M.w1[0], M.w1[2], n[0], n[1], n[2], sx, sy);
-                if constexpr (PLAIN) {
+                if constexpr (!WALL) {
                     collide_free<VISC>(P, s, M.rho, M.w1[1], sx, sy);
                 } else {
                     double Ax = 0.0, Ay = 0.0;
@@ -174,10 +175,10 @@ __device__ __forceinline__ void march_strip(const KParams& P, const double* __re
 #pragma unroll
             for (int k = 0; k < 9; ++k) M.f[k] = f[k];
             M.rho = rho;
-            if (!PLAIN && c < lo) break;
+            if (PART && c < lo) break;
             if (t == T - 1) {
-                if ((PLAIN || c <= hi) && store) {
-                    double* o = gout + (long long)(PLAIN || rows ? c : wrapx(c, P.ny)) * P.pitch;
+                if ((!WALL || c <= hi) && store) {
+                    double* o = gout + (long long)(!WALL || rows ? c : wrapx(c, P.ny)) * P.pitch;
 #pragma unroll
                     for (int k = 0; k < 9; ++k) {
                         unsigned at = 8 * xc;
@@ -189,25 +190,25 @@ __device__ __forceinline__ void march_strip(const KParams& P, const double* __re
                 // the next level's pull of row c - 1
                 f[2] = M.a[0]; f[5] = M.a[1]; f[6] = M.a[2];
                 f[0] = M.a[3]; f[1] = M.a[4]; f[3] = M.a[5];
-                if (PLAIN || c <= hi) {
+                if (!WALL || c <= hi) {
                     f[4] = s[4];
                     f[7] = X::right(s[7]);
                     f[8] = X::left(s[8]);
-                    const bool b = !PLAIN && rows && c == 1;  // reflected at the bottom wall
+                    const bool b = WALL && rows && c == 1;  // reflected at the bottom wall
                     M.a[0] = b ? s[4] : M.up[0];
                     M.a[1] = b ? s[7] : M.up[1];
                     M.a[2] = b ? s[8] : M.up[2];
                     M.a[3] = s[0];
                     M.a[4] = X::left(s[1]);
                     M.a[5] = X::right(s[3]);
-                    const bool u = !PLAIN && rows && c == top;  // kept: the top wall reflects it
+                    const bool u = WALL && rows && c == top;  // kept: the top wall reflects it
                     M.up[0] = s[2];
                     M.up[1] = u ? s[5] : X::left(s[5]);
                     M.up[2] = u ? s[6] : X::right(s[6]);
                 } else {  // the solid row above: row c - 1 = top is reflected
                     f[4] = M.up[0]; f[7] = M.up[1]; f[8] = M.up[2];
                 }
-                if (!PLAIN && GEO == GEO_WET && P.wet) {
+                if (WALL && GEO == GEO_WET && P.wet) {
                     if (c == 2) wet_node_bottom(f, M.F[0], M.F[1]);
                     if (c - 1 == top) wet_node_top(f, M.F[0], M.F[1]);
                 }
@@ -220,21 +221,34 @@ __device__ __forceinline__ void march_strip(const KParams& P, const double* __re
     auto at = [&](int y) { return rows ? y : wrapx(y, P.ny); };
     double pf[9];  // the next row, on its way
     march_load<false, X>(P, gin, b, at(first), pf);
-    // rows [s0, s1] are plain, as is the row after each, which is loaded meanwhile
+    // Rows up to s1 touch no wall, nor does the row after each, which is loaded meanwhile; from s0
+    // on every level is in use. A segment whose first row lies clear of the bottom wall (or seam)
+    // fills its levels without wall rules.
     const int s0 = rows && y0 + H < 2 * T + 2 ? 2 * T + 2 : y0 + H;
     const int lim = rows ? top - 2 : P.ny - 3;
     const int s1 = last - 1 < lim ? last - 1 : lim;
-    for (int i = first; i <= last; ++i) {
-        double f[9];
+    int i = first;
+    double f[9];
+    const std::true_type yes;
+    const std::false_type no;
+    auto next = [&](int r) {  // takes the row on its way and starts the loads of row r
+#pragma unroll
+        for (int k = 0; k < 9; ++k) f[k] = pf[k];
+        march_load<true, X>(P, gin, b, r, pf);
+    };
+    if (first >= 2 && s0 < s1)
+        for (; i < s0; ++i) {
+            next(i + 1);
+            row(no, yes, i, f);
+        }
+    for (; i <= last; ++i) {
         if (i >= s0 && i < s1) {
             // two rows a turn, so that what one row held and what it pulled swap registers
             for (; i < s1; i += 2) {
 #pragma unroll
                 for (int r = 0; r < 2; ++r) {
-#pragma unroll
-                    for (int k = 0; k < 9; ++k) f[k] = pf[k];
-                    march_load<true, X>(P, gin, b, i + r + 1, pf);
-                    row(std::true_type{}, i + r, f);
+                    next(i + r + 1);
+                    row(no, no, i + r, f);
                 }
             }
             if (i > last) break;
@@ -247,7 +261,7 @@ __device__ __forceinline__ void march_strip(const KParams& P, const double* __re
             if (i == top) wet_node_top(f, rt[xc], rt[P.plane + xc]);
         }
         if (i < load_last) march_load<false, X>(P, gin, b, at(i + 1), pf);
-        row(std::false_type{}, i, f);
+        row(yes, yes, i, f);
     }
 }
 
