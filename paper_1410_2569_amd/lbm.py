@@ -187,6 +187,15 @@ def check(rc: int, ctx=None):
         raise LBMError(rc, msg)
 
 
+def _new_bytes(n: int):
+    """A bytes object of n bytes yet to be filled, and its address. Filled once, before anyone else
+    holds it: no zeroed buffer and no copy of a state that may take hundreds of megabytes."""
+    make = C.pythonapi.PyBytes_FromStringAndSize
+    make.restype, make.argtypes = C.py_object, [C.c_char_p, C.c_ssize_t]
+    b = make(None, n)
+    return b, C.cast(C.c_char_p(b), C.c_void_p)
+
+
 def maxwell_cs(a: float, b: float, R: float, T: float):
     """(rho_v, rho_l, p0) of the Carnahan-Starling Maxwell construction (library's solver)."""
     rv, rl, p0 = C.c_double(), C.c_double(), C.c_double()
@@ -419,9 +428,9 @@ class Sim:
     def save_state(self) -> bytes:
         n = C.c_size_t()
         self._chk(lib().lbm_state_size(self.h, C.byref(n)))
-        buf = C.create_string_buffer(n.value)
-        self._chk(lib().lbm_save_state(self.h, buf, n.value))
-        return buf.raw
+        blob, at = _new_bytes(n.value)
+        self._chk(lib().lbm_save_state(self.h, at, n.value))
+        return blob
 
     def load_state(self, blob: bytes):
         self._chk(lib().lbm_load_state(self.h, C.c_char_p(blob), len(blob)))
@@ -600,9 +609,9 @@ class Batch:
         """Checkpoint blob of one instance, loadable by Sim.load_state."""
         q = self.params[index]
         n = 32 + 9 * q.nx * q.ny * 8
-        buf = C.create_string_buffer(n)
-        self._chk(lib().lbm_batch_save_state(self.h, int(index), buf, n))
-        return buf.raw
+        blob, at = _new_bytes(n)
+        self._chk(lib().lbm_batch_save_state(self.h, int(index), at, n))
+        return blob
 
     def f(self, index: int) -> np.ndarray:
         q = self.params[index]
