@@ -300,7 +300,7 @@ __global__ __launch_bounds__(256) void k_batch_contact_line(const InstDesc* __re
 // have nothing to do. The arithmetic and its order are those of the lattice alone.
 __global__ __launch_bounds__(256) void k_batch_obs(const InstDesc* __restrict__ inst,
                                                    const double* __restrict__ y_wall, int cur) {
-    __shared__ ObsLds lds;
+    __shared__ ObsLds<kObsRows> lds;
     const InstDesc* D = inst + blockIdx.y;
     const KParams& P = D->P;
     const int nbx = (P.nx + 63) / 64, nby = (P.y_hi - P.y_lo + kObsRows) / kObsRows;
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(256) void k_batch_obs(const InstDesc* __restrict__ 
     const double yw = y_wall ? y_wall[blockIdx.y] : (P.wet ? 1.0 : 0.5);
     const ObsArgs A{P.rho_mid, yw + 3.0, -__builtin_huge_val(), __builtin_huge_val(),
                     0.5 * P.nx, yw};
-    obs_tile<false>(P, gptr(D->g[cur]), gptr(D->gw), A, blockIdx.x % nbx, blockIdx.x / nbx, nbx,
+    obs_tile<false, kObsRows>(P, gptr(D->g[cur]), gptr(D->gw), A, blockIdx.x % nbx, blockIdx.x / nbx, nbx,
                     gptr(D->part), lds);
 }
 

@@ -211,12 +211,12 @@ __global__ __launch_bounds__(256) void k_repack(const double* __restrict__ src, 
 // ------------------------------------------------------------------------------------------------
 // Observables (obs_tile, obs_final_block)
 // ------------------------------------------------------------------------------------------------
-template <bool PRE>
+template <bool PRE, int ROWS>
 __global__ __launch_bounds__(256) void k_obs(KParams P, const double* __restrict__ gin,
                                              const double* __restrict__ gw, ObsArgs A,
                                              double* __restrict__ part) {
-    __shared__ ObsLds lds;
-    obs_tile<PRE>(P, gin, gw, A, blockIdx.x, blockIdx.y, gridDim.x, part, lds);
+    __shared__ ObsLds<ROWS> lds;
+    obs_tile<PRE, ROWS>(P, gin, gw, A, blockIdx.x, blockIdx.y, gridDim.x, part, lds);
 }
 
 __global__ __launch_bounds__(256) void k_obs_final(const double* __restrict__ part, int nblk,
@@ -589,10 +589,15 @@ int obs_blocks(const KParams& P) { return obs_rows(P); }
 
 hipError_t launch_obs(const KParams& P, const double* gin, const double* gw, const ObsArgs& A,
                       double* part, double* out, hipStream_t s, bool pre) {
-    const dim3 g((P.nx + 63) / 64, (P.y_hi - P.y_lo + kObsRows) / kObsRows);
-    if (pre) hipLaunchKernelGGL(k_obs<true>, g, dim3(256), 0, s, P, gin, gw, A, part);
-    else hipLaunchKernelGGL(k_obs<false>, g, dim3(256), 0, s, P, gin, gw, A, part);
-    hipError_t e = hipGetLastError();
+    auto go = [&](auto rows) {
+        constexpr int R = decltype(rows)::value;
+        const dim3 g((P.nx + 63) / 64, (P.y_hi - P.y_lo + R) / R);
+        if (pre) hipLaunchKernelGGL((k_obs<true, R>), g, dim3(256), 0, s, P, gin, gw, A, part);
+        else hipLaunchKernelGGL((k_obs<false, R>), g, dim3(256), 0, s, P, gin, gw, A, part);
+        return hipGetLastError();
+    };
+    hipError_t e = obs_rows(P) < 512 ? go(std::integral_constant<int, kObsRowsSmall>{})
+                                     : go(std::integral_constant<int, kObsRows>{});
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_obs_final, dim3(1), dim3(256), 0, s, part, obs_rows(P), out);
     return hipGetLastError();

@@ -7,53 +7,63 @@
 
 namespace lbm {
 
-// LDS of obs_tile: density and psi of 64 x 8 nodes and one ring, partials of 4 waves.
-constexpr int kObsRows = 8;
+// LDS of obs_tile: density and psi of 64 x ROWS nodes and one ring, partials of 4 waves.
+template <int ROWS>
 struct ObsLds {
-    double rho[(kObsRows + 2) * 66], psi[(kObsRows + 2) * 66];
-    double red[kObsRows / 4][4][O_NQ];
+    double rho[(ROWS + 2) * 66], psi[(ROWS + 2) * 66];
+    double red[ROWS / 4][4][O_NQ];
 };
+// Rows of a block: 8, or 4 on lattices with fewer than 256 blocks of 8, whose compute units would
+// wait for one block's longer chain (100 x 50: 45.4 us per call with 8, 40.7 with 4; two passes
+// over the lattice took 44.1).
+constexpr int kObsRows = 8, kObsRowsSmall = 4;
 
-// Observables of the 64 x 8 nodes at (64 bx, y_lo + 8 by), by 256 threads, two nodes each: density
+// Observables of the 64 x ROWS nodes at (64 bx, y_lo + ROWS by), by 256 threads: density
 // and psi of the nodes and the ring around them are formed in LDS from the pulled populations (no
 // field goes through memory), then every wave reduces its 64 nodes of each row. Writes the O_NQ
-// partials of each half of 64 x 4 nodes, part[(2 by + half) * nbx + bx], where it holds fluid rows.
+// partials of each 64 x 4 nodes, part[(ROWS / 4 by + r) * nbx + bx], where they hold fluid rows.
 // Waves without an interface crossing or a node that is not finite (most) skip those sums, whose
 // every term is 0. What bounds it: one read of the populations; the ring's pulls come from L2.
-template <bool PRE>
+// 1024 x 512, a call on held populations: 67.8 us with two passes and their fields, 57.5 so.
+template <bool PRE, int ROWS>
 __device__ __forceinline__ void obs_tile(const KParams& P, const double* __restrict__ gin,
                                          const double* __restrict__ gw, const ObsArgs& A, int bx,
-                                         int by, int nbx, double* __restrict__ part, ObsLds& L) {
-    constexpr int LW = 66, NR = kObsRows / 4, NRING = 2 * LW + 2 * kObsRows;
+                                         int by, int nbx, double* __restrict__ part, ObsLds<ROWS>& L) {
+    constexpr int LW = 66, NR = ROWS / 4, NRING = 2 * LW + 2 * ROWS;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int x0 = bx * 64, y0 = P.y_lo + by * kObsRows, x = x0 + lane;
-    double f[NR][9];
-    bool act[NR];
-    // density and psi at lattice slot (gx, gy); 0 where the slot holds none
-    auto slot = [&](int gx, int gy, double g[9], double& rho) {
+    const int x0 = bx * 64, y0 = P.y_lo + by * ROWS, x = x0 + lane;
+    // every pull is issued before the first psi: two nodes and, for some threads, a slot of the ring
+    double f[NR][9], g[9];
+    bool act[NR], has[NR], hasg = false;
+    auto pull = [&](int gx, int gy, double p[9]) {
         int sx, sy;
-        rho = 0.0;
-        if (!slot_source(P, gx, gy, sx, sy)) return 0.0;
-        node_populations<PRE>(P, gin, sx, sy, g);
-        rho = sum9(g);
-        return psi_of_rho(P, rho);
+        if (!slot_source(P, gx, gy, sx, sy)) return false;
+        node_populations<PRE>(P, gin, sx, sy, p);
+        return true;
     };
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        const int ly = 4 * r + wv, y = y0 + ly;
+        const int y = y0 + 4 * r + wv;
         act[r] = x < P.nx && y <= P.y_hi && !is_solid_node(P, x, y);
-        const int l = (ly + 1) * LW + lane + 1;
-        L.psi[l] = slot(x, y, f[r], L.rho[l]);
+        has[r] = pull(x, y, f[r]);
     }
-    for (int h = threadIdx.x; h < NRING; h += 256) {
-        int lx, ly;
-        if (h < LW) { lx = h; ly = 0; }
-        else if (h < 2 * LW) { lx = h - LW; ly = kObsRows + 1; }
-        else if (h < 2 * LW + kObsRows) { lx = 0; ly = h - 2 * LW + 1; }
-        else { lx = LW - 1; ly = h - 2 * LW - kObsRows + 1; }
-        double g[9];
-        L.psi[ly * LW + lx] = slot(x0 - 1 + lx, y0 - 1 + ly, g, L.rho[ly * LW + lx]);
-    }
+    static_assert(NRING <= 256, "at most one slot of the ring per thread");
+    const int h = threadIdx.x;
+    int lx, ly;
+    if (h < LW) { lx = h; ly = 0; }
+    else if (h < 2 * LW) { lx = h - LW; ly = ROWS + 1; }
+    else if (h < 2 * LW + ROWS) { lx = 0; ly = h - 2 * LW + 1; }
+    else { lx = LW - 1; ly = h - 2 * LW - ROWS + 1; }
+    if (h < NRING) hasg = pull(x0 - 1 + lx, y0 - 1 + ly, g);
+    // density and psi into slot l; 0 where the slot holds none
+    auto put = [&](bool v, const double p[9], int l) {
+        const double rho = v ? sum9(p) : 0.0;
+        L.rho[l] = rho;
+        L.psi[l] = v ? psi_of_rho(P, rho) : 0.0;
+    };
+#pragma unroll
+    for (int r = 0; r < NR; ++r) put(has[r], f[r], (4 * r + wv + 1) * LW + lane + 1);
+    if (h < NRING) put(hasg, g, ly * LW + lx);
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
