@@ -1234,7 +1234,6 @@ struct lbm_batch {
     int* d_flag;
     lbm::MarchSeg* d_segs;  // work-list of the marching strips
     int nsegs;              // 0: schedule 2 runs tiles
-    int visc;               // as in launch_batch_march
     double* d_obs;          // 16 sums per instance, then the contact planes
     int obs_blocks;         // most blocks of an instance's observables
     std::vector<double*> part, fin;
@@ -1479,9 +1478,6 @@ static int batch_create_impl(const lbm_params* p, int32_t count,
         e = host_copy(s, b->d_segs, B.segs.data(), B.segs.size() * sizeof(lbm::MarchSeg),
                       hipMemcpyHostToDevice);
     if (e != hipSuccess) { delete b; return create_fail(LBM_E_HIP, "create: tile table copy", e); }
-    b->visc = b->kp[0].visc_const ? 1 : 2;
-    for (const KParams& k : b->kp)
-        if (k.visc_const != b->kp[0].visc_const) b->visc = 0;
     if ((e = hipStreamSynchronize(s)) != hipSuccess) { delete b; return create_fail(LBM_E_HIP, "create hipStreamSynchronize", e); }
     // persistent grid: co-resident workgroups only (occupancy x compute units)
     int dev = 0, cus = 0;
@@ -1532,8 +1528,8 @@ static hipError_t batch_launch(lbm_batch* b, int64_t n, int src, int dst,
                                const lbm::Checkpoints* ck = nullptr) {
     const int k = batch_next_steps(b, n);
     if (k == lbm::kMarchSteps)
-        return lbm::launch_batch_march(b->geo, b->eos, b->visc, b->d_inst, b->d_segs, b->nsegs, src,
-                                       dst, ck, b->stream);
+        return lbm::launch_batch_march(b->geo, b->eos, b->d_inst, b->d_segs, b->nsegs, src, dst, ck,
+                                       b->stream);
     if (k == 2)
         return lbm::launch_batch_step2(b->tune.tile, b->geo, b->eos, b->d_inst, b->d_tile_inst,
                                        b->ntiles, src, dst, ck, b->stream);

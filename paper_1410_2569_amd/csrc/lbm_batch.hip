@@ -79,7 +79,7 @@ k_batch_step2(
 }
 
 // kMarchSteps steps per launch over the ensemble's list of segments, one per wave (march_strip).
-template <int GEO, int EOS, int VISC>
+template <int GEO, int EOS>
 __global__ __launch_bounds__(64 * kMarchWaves, 2) void k_batch_march(
     const InstDesc* __restrict__ inst, const MarchSeg* __restrict__ segs, int n, int src, int dst,
     const Checkpoints* __restrict__ ck) {
@@ -89,10 +89,16 @@ __global__ __launch_bounds__(64 * kMarchWaves, 2) void k_batch_march(
     const MarchSeg S = segs[w];
     const InstDesc* D = inst + S.inst;
     const KParams P = D->P;
-    march_strip<kMarchSteps, GEO, EOS, VISC, DppLane>(P, inst_buffer(D, ck, S.inst, src),
-                                                      inst_buffer(D, ck, S.inst, dst),
-                                                      gptr(D->gw), S.x0, S.y0, S.y1,
-                                                      threadIdx.x & 63);
+    const double* gin = inst_buffer(D, ck, S.inst, src);
+    double* gout = inst_buffer(D, ck, S.inst, dst);
+    const int lane = threadIdx.x & 63;
+    // one or two viscosities: a branch per wave here, not one per row and level inside
+    if (P.visc_const)
+        march_strip<kMarchSteps, GEO, EOS, 1, DppLane>(P, gin, gout, gptr(D->gw), S.x0, S.y0, S.y1,
+                                                       lane);
+    else
+        march_strip<kMarchSteps, GEO, EOS, 2, DppLane>(P, gin, gout, gptr(D->gw), S.x0, S.y0, S.y1,
+                                                       lane);
 }
 
 // Bounded wait (thread 0 of a workgroup) until *ctr >= target. Returns 0 when the run was
@@ -581,23 +587,16 @@ hipError_t launch_batch_adj_gw(const AdjInst* inst, int count, int max_nx, int k
     return hipGetLastError();
 }
 
-hipError_t launch_batch_march(int geo, int eos, int visc, const InstDesc* inst,
-                              const MarchSeg* segs, int n, int src, int dst,
-                              const Checkpoints* ck, hipStream_t s) {
+hipError_t launch_batch_march(int geo, int eos, const InstDesc* inst, const MarchSeg* segs, int n,
+                              int src, int dst, const Checkpoints* ck, hipStream_t s) {
     return dispatch(geo, eos, [&](auto g, auto e) {
         constexpr int G = decltype(g)::value, E = decltype(e)::value;
         if constexpr (G == GEO_MASK) {
             return hipErrorInvalidValue;
         } else {
-            auto go = [&](auto v) {
-                hipLaunchKernelGGL((k_batch_march<G, E, decltype(v)::value>),
-                                   dim3((n + kMarchWaves - 1) / kMarchWaves),
-                                   dim3(64 * kMarchWaves), 0, s, inst, segs, n, src, dst, ck);
-                return hipGetLastError();
-            };
-            if (visc == 1) return go(std::integral_constant<int, 1>{});
-            if (visc == 2) return go(std::integral_constant<int, 2>{});
-            return go(std::integral_constant<int, 0>{});
+            hipLaunchKernelGGL((k_batch_march<G, E>), dim3((n + kMarchWaves - 1) / kMarchWaves),
+                               dim3(64 * kMarchWaves), 0, s, inst, segs, n, src, dst, ck);
+            return hipGetLastError();
         }
     });
 }

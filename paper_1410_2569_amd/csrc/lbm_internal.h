@@ -73,10 +73,8 @@ int march_rows(const MarchShape* m, int count);
 void march_segments(const MarchShape& m, int inst, int y_lo, int h, std::vector<MarchSeg>* out);
 hipError_t launch_march(const KParams& P, int h, const double* gin, double* gout, const double* gw,
                         hipStream_t s);
-// visc: 1 every instance has one viscosity, 2 none has, 0 some have
-hipError_t launch_batch_march(int geo, int eos, int visc, const InstDesc* inst,
-                              const MarchSeg* segs, int n, int src, int dst,
-                              const Checkpoints* ck, hipStream_t s);
+hipError_t launch_batch_march(int geo, int eos, const InstDesc* inst, const MarchSeg* segs, int n,
+                              int src, int dst, const Checkpoints* ck, hipStream_t s);
 // Multi-step tiles (lbm_steps.h): kTileSteps steps per launch on lattices too small to fill the GPU.
 constexpr int kTileSteps = 4;
 // Tile of a lattice of nx columns and `rows` fluid rows (for launch_steps), or -1 where the
