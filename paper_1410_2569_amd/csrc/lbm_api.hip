@@ -959,14 +959,11 @@ int lbm_observables_of_state(const lbm_params* p, const double* d_f, const doubl
 int lbm_read_rho(lbm_ctx* c, double* host, size_t count) {
     if (!c || !host) return LBM_E_INVAL;
     if (count < (size_t)c->p.nx * c->p.ny) return LBM_E_SIZE;
-    const KParams& P = c->kp;
     double* scratch = c->g[c->cur ^ 1];
-    hipError_t e = lbm::launch_zero(scratch, (size_t)P.plane * sizeof(double), c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, "read_rho memset");
-    e = lbm::launch_rho_psi(P, c->g[c->cur], c->psi, scratch, c->stream);
+    hipError_t e = lbm::launch_read(c->kp, c->g[c->cur], scratch, true, c->stream);
     if (e == hipSuccess)
-        e = download_field(c->stream, scratch, P.plane, P.pitch, 1, P.ny, P.nx, scratch + P.plane,
-                           host);
+        e = host_copy(c->stream, host, scratch, (size_t)c->p.nx * c->p.ny * sizeof(double),
+                      hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(c, e, "read_rho");
     return LBM_OK;
 }
@@ -977,9 +974,7 @@ int lbm_read_f(lbm_ctx* c, double* host, size_t count) {
     const KParams& P = c->kp;
     double* scratch = c->g[c->cur ^ 1];
     const size_t n = (size_t)9 * P.nx * P.ny;
-    hipError_t e = lbm::launch_zero(scratch, n * sizeof(double), c->stream);
-    if (e != hipSuccess) return hip_fail(c, e, "read_f memset");
-    e = lbm::launch_pull(P, c->g[c->cur], scratch, c->stream, true);
+    hipError_t e = lbm::launch_read(P, c->g[c->cur], scratch, false, c->stream);
     if (e == hipSuccess) e = host_copy(c->stream, host, scratch, n * sizeof(double), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(c, e, "read_f");
     return LBM_OK;
@@ -1714,8 +1709,7 @@ int lbm_batch_read_f(lbm_batch* b, int32_t index, double* host, size_t count) {
     const lbm::InstDesc& d = b->desc[index];
     double* scratch = d.g[b->cur ^ 1];  // the idle buffer: the next step overwrites it
     const size_t n = (size_t)9 * P.nx * P.ny;
-    hipError_t e = lbm::launch_zero(scratch, n * sizeof(double), b->stream);
-    if (e == hipSuccess) e = lbm::launch_pull(P, d.g[b->cur], scratch, b->stream, true);
+    hipError_t e = lbm::launch_read(P, d.g[b->cur], scratch, false, b->stream);
     if (e == hipSuccess) e = host_copy(b->stream, host, scratch, n * sizeof(double), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "batch read");
     return LBM_OK;

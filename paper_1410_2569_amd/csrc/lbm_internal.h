@@ -99,15 +99,13 @@ struct DropletArgs {
 hipError_t launch_droplets(const KParams& P, const DropletArgs& D, double* rho, hipStream_t s);
 hipError_t launch_fp64_probe(const double* a, const double* b, double* sq, double* quot,
                              long long n, hipStream_t s);
-// dense: fout is [9][ny][nx] (otherwise [9][ny][pitch])
-hipError_t launch_pull(const KParams& P, const double* gin, double* fout, hipStream_t s,
-                       bool dense = false);
+// every node of the lattice, 0 on solid ones: pre-collision populations [9][ny][nx], or with rho
+// the density [ny][nx]
+hipError_t launch_read(const KParams& P, const double* gin, double* out, bool rho, hipStream_t s);
 // `planes` planes of ny x nx doubles from one row/plane layout to another (device memory)
 hipError_t launch_repack(const double* src, long long src_plane, int src_pitch, double* dst,
                          long long dst_plane, int dst_pitch, int nx, int ny, int planes,
                          hipStream_t s);
-hipError_t launch_rho_psi(const KParams& P, const double* gin, double* psi, double* rho,
-                          hipStream_t s);
 hipError_t launch_contact_line(const KParams& P, const double* gin, int row, double mid,
                                double* out, hipStream_t s);
 int obs_blocks(const KParams& P);

@@ -137,14 +137,13 @@ __global__ __launch_bounds__(64 * kMarchWaves, 2) void k_march(
                                                       threadIdx.x & 63);
 }
 
-// psi pass of the two-pass schedule and density read-out; also writes the mirrored ghost rows.
+// psi pass of the two-pass schedule; also writes the mirrored ghost rows.
 __global__ __launch_bounds__(256) void k_psi(KParams P, const double* __restrict__ gin,
-                                             double* __restrict__ psi_g,
-                                             double* __restrict__ rho_out) {
+                                             double* __restrict__ psi_g) {
     const int x = blockIdx.x * 64 + (threadIdx.x & 63);
     const int y = P.y_lo + blockIdx.y * 4 + (threadIdx.x >> 6);
     if (x >= P.nx || y > P.y_hi) return;
-    psi_node(P, gin, psi_g, rho_out, x, y);
+    psi_node(P, gin, psi_g, nullptr, x, y);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -177,18 +176,24 @@ __global__ __launch_bounds__(256) void k_init(KParams P, const double* __restric
     }
 }
 
-// Pre-collision populations f^n (pulled) into a [9][ny][pitch] buffer, or with `dense` a
-// [9][ny][nx] one.
-__global__ __launch_bounds__(256) void k_pull(KParams P, const double* __restrict__ gin,
-                                              double* __restrict__ fout, int dense) {
+// Read-out of every node of the lattice, dense and complete (0 on solid nodes), so that the copy to
+// the host is all that follows: pre-collision populations f^n [9][ny][nx], or with RHO the density
+// [ny][nx].
+template <bool RHO>
+__global__ __launch_bounds__(256) void k_read(KParams P, const double* __restrict__ gin,
+                                              double* __restrict__ out) {
     const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = P.y_lo + blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (x >= P.nx || y > P.y_hi || is_solid_node(P, x, y)) return;
-    double f[9];
-    pull9_any(P, gin, x, y, f);
-    const long long pl = dense ? (long long)P.nx * P.ny : P.plane;
-    const long long i = dense ? (long long)y * P.nx + x : (long long)y * P.pitch + x;
-    for (int a = 0; a < 9; ++a) fout[a * pl + i] = f[a];
+    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
+    if (x >= P.nx || y >= P.ny) return;
+    double f[9] = {};
+    if (y >= P.y_lo && y <= P.y_hi && !is_solid_node(P, x, y)) pull9_any(P, gin, x, y, f);
+    const long long pl = (long long)P.nx * P.ny, i = (long long)y * P.nx + x;
+    if (RHO) {
+        out[i] = sum9(f);
+    } else {
+#pragma unroll
+        for (int a = 0; a < 9; ++a) out[a * pl + i] = f[a];
+    }
 }
 
 // Copy of `planes` planes of ny rows of nx doubles between two layouts in device memory: rows
@@ -462,8 +467,7 @@ void tile_shape(int tile, int* tx, int* ty) {
 hipError_t launch_step(const KParams& P, int schedule, int tile, const double* gin, double* gout,
                        double* psi, const double* gw, hipStream_t s) {
     if (schedule == 1) {
-        hipLaunchKernelGGL(k_psi, node_grid(P), dim3(256), 0, s, P, gin, psi,
-                           (double*)nullptr);
+        hipLaunchKernelGGL(k_psi, node_grid(P), dim3(256), 0, s, P, gin, psi);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         return launch_step_t<64, 4, false>(P, gin, gout, psi, gw, s);
@@ -556,9 +560,10 @@ hipError_t launch_init(const KParams& P, const double* rho0, double* g, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_pull(const KParams& P, const double* gin, double* fout, hipStream_t s,
-                       bool dense) {
-    hipLaunchKernelGGL(k_pull, node_grid(P), dim3(256), 0, s, P, gin, fout, dense ? 1 : 0);
+hipError_t launch_read(const KParams& P, const double* gin, double* out, bool rho, hipStream_t s) {
+    const dim3 g((P.nx + 63) / 64, (P.ny + 3) / 4);
+    if (rho) hipLaunchKernelGGL(k_read<true>, g, dim3(256), 0, s, P, gin, out);
+    else hipLaunchKernelGGL(k_read<false>, g, dim3(256), 0, s, P, gin, out);
     return hipGetLastError();
 }
 
@@ -570,12 +575,6 @@ hipError_t launch_repack(const double* src, long long src_plane, int src_pitch, 
     const unsigned blocks = (unsigned)std::min<long long>((n + 255) / 256, 8192);
     hipLaunchKernelGGL(k_repack, dim3(blocks), dim3(256), 0, s, src, src_plane, src_pitch, dst,
                        dst_plane, dst_pitch, nx, ny, planes);
-    return hipGetLastError();
-}
-
-hipError_t launch_rho_psi(const KParams& P, const double* gin, double* psi, double* rho,
-                          hipStream_t s) {
-    hipLaunchKernelGGL(k_psi, node_grid(P), dim3(256), 0, s, P, gin, psi, rho);
     return hipGetLastError();
 }
 
