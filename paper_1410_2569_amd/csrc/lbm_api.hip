@@ -52,7 +52,7 @@ struct lbm_ctx {
 namespace {
 
 constexpr size_t kAlign = 256;
-// Host copies from this size on go through pinned buffers of kStageChunk bytes.
+// Copies to the host from this size on go through pinned buffers of kStageChunk bytes.
 constexpr size_t kStagedBytes = size_t(8) << 20, kStageChunk = size_t(4) << 20;
 constexpr int kCopyThreads = 4;
 
@@ -70,17 +70,17 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 // Every copy between host and device memory is one contiguous synchronous transfer made after
 // the stream's queued work has completed: pitched fields are packed or unpacked on the device
 // (k_repack) next to a dense staging copy. The host buffers of this API are ordinary pageable
-// memory (large ones are copied through pinned buffers, staged_copy); a synchronous copy is
+// memory (large read-outs go through pinned buffers, staged_read); a synchronous copy is
 // complete when it returns, and the preceding synchronisation
 // orders it after the stream's kernels (every kernel enqueued later sees it). No strided (2D)
 // copy is used: with a kernel tracer attached those have been observed not to deliver their data.
-hipError_t staged_copy(hipStream_t s, char* dst, const char* src, size_t bytes, bool to_host);
+hipError_t staged_read(hipStream_t s, char* dst, const char* src, size_t bytes);
 
 hipError_t host_copy(hipStream_t s, void* dst, const void* src, size_t bytes, hipMemcpyKind kind) {
     hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
-    if (bytes >= kStagedBytes)
-        return staged_copy(s, (char*)dst, (const char*)src, bytes, kind == hipMemcpyDeviceToHost);
+    if (kind == hipMemcpyDeviceToHost && bytes >= kStagedBytes)
+        return staged_read(s, (char*)dst, (const char*)src, bytes);
     return hipMemcpy(dst, src, bytes, kind);
 }
 
@@ -102,45 +102,35 @@ void parallel_memcpy(char* dst, const char* src, size_t n) {
         if (t.joinable()) t.join();
 }
 
-// A large copy between pageable host memory and the device, through two pinned buffers of the call's
+// A large copy from the device into pageable host memory, through two pinned buffers of the call's
 // own: one is on its way over PCIe (57 GB/s) while threads copy the other, which also spreads the
-// page faults of a fresh host array. hipMemcpy on pageable memory reaches 17 GB/s, 10 GB/s into a
-// fresh array. From the device into one: 151 MB 16.1 -> 7.1 ms, 38 MB 3.6 -> 1.9, 12 MB 1.0 -> 0.65
-// (2 threads 9.8, 2.1, 0.76; 8 threads 8.9, 2.2, 0.71).
-hipError_t staged_copy(hipStream_t s, char* dst, const char* src, size_t bytes, bool to_host) {
+// page faults of a fresh host array. hipMemcpy reaches 17 GB/s into pageable memory, 10 GB/s into a
+// fresh array: 151 MB 16.1 -> 7.1 ms, 38 MB 3.6 -> 1.9, 12 MB 1.0 -> 0.65 (2 threads 9.8, 2.1, 0.76;
+// 8 threads 8.9, 2.2, 0.71). Towards the device hipMemcpy stays: its host pages are there already,
+// and creating a 1500 x 1001 lattice took 15.0-20.7 ms with staged uploads, 11.9-16.1 without.
+hipError_t staged_read(hipStream_t s, char* dst, const char* src, size_t bytes) {
     char* buf[2] = {};
     hipEvent_t ev[2] = {};
     hipError_t e = hipHostMalloc((void**)&buf[0], 2 * kStageChunk, hipHostMallocDefault);
     if (e != hipSuccess) {  // no pinned memory to be had
         (void)hipGetLastError();
-        return hipMemcpy(dst, src, bytes, to_host ? hipMemcpyDeviceToHost : hipMemcpyHostToDevice);
+        return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
     }
     buf[1] = buf[0] + kStageChunk;
     for (int k = 0; k < 2 && e == hipSuccess; ++k)
         e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
     const size_t n = (bytes + kStageChunk - 1) / kStageChunk;
     auto len = [&](size_t i) { return std::min(kStageChunk, bytes - i * kStageChunk); };
-    auto start = [&](size_t i) {  // chunk i between its buffer and the device
-        hipError_t r = to_host ? hipMemcpyAsync(buf[i & 1], src + i * kStageChunk, len(i),
-                                                hipMemcpyDeviceToHost, s)
-                               : hipMemcpyAsync(dst + i * kStageChunk, buf[i & 1], len(i),
-                                                hipMemcpyHostToDevice, s);
+    auto start = [&](size_t i) {  // chunk i into its buffer
+        hipError_t r = hipMemcpyAsync(buf[i & 1], src + i * kStageChunk, len(i),
+                                      hipMemcpyDeviceToHost, s);
         return r == hipSuccess ? hipEventRecord(ev[i & 1], s) : r;
     };
-    if (to_host) {
-        if (e == hipSuccess) e = start(0);
-        for (size_t i = 0; i < n && e == hipSuccess; ++i) {
-            if (i + 1 < n) e = start(i + 1);
-            if (e == hipSuccess) e = hipEventSynchronize(ev[i & 1]);
-            if (e == hipSuccess) parallel_memcpy(dst + i * kStageChunk, buf[i & 1], len(i));
-        }
-    } else {
-        for (size_t i = 0; i < n && e == hipSuccess; ++i) {
-            if (i >= 2) e = hipEventSynchronize(ev[i & 1]);  // the buffer's last chunk has left
-            if (e != hipSuccess) break;
-            parallel_memcpy(buf[i & 1], src + i * kStageChunk, len(i));
-            e = start(i);
-        }
+    if (e == hipSuccess) e = start(0);
+    for (size_t i = 0; i < n && e == hipSuccess; ++i) {
+        if (i + 1 < n) e = start(i + 1);
+        if (e == hipSuccess) e = hipEventSynchronize(ev[i & 1]);
+        if (e == hipSuccess) parallel_memcpy(dst + i * kStageChunk, buf[i & 1], len(i));
     }
     const hipError_t es = hipStreamSynchronize(s);
     for (int k = 0; k < 2; ++k)
