@@ -11,7 +11,7 @@
 #include <functional>
 #include <mutex>
 #include <string>
-#include <system_error>
+#include <exception>
 #include <thread>
 #include <vector>
 
@@ -93,7 +93,7 @@ void parallel_memcpy(char* dst, const char* src, size_t n) {
         const size_t m = std::min(part, n - o);
         try {
             th[k] = std::thread([=] { std::memcpy(dst + o, src + o, m); });
-        } catch (const std::system_error&) {
+        } catch (const std::exception&) {
             std::memcpy(dst + o, src + o, m);
         }
     }
@@ -1834,10 +1834,9 @@ int lbm_batch_forward_ckpt(lbm_batch* b, int64_t nsteps, int32_t K, void* d_adj,
     for (int k = 0; k < b->count; ++k)
         ck[k] = {(double*)(w + L.off[k] + L.A[k].off_ck),
                  (long long)(L.A[k].fbytes / sizeof(double))};
-    const lbm::Checkpoints* d_ck = (const lbm::Checkpoints*)(w + L.off_inst);
+    lbm::Checkpoints* d_ck = (lbm::Checkpoints*)(w + L.off_inst);
     static_assert(sizeof(lbm::Checkpoints) <= sizeof(lbm::AdjInst), "the table fits");
-    hipError_t e = host_copy(b->stream, w + L.off_inst, ck.data(),
-                             ck.size() * sizeof(lbm::Checkpoints), hipMemcpyHostToDevice);
+    hipError_t e = lbm::launch_checkpoints(ck.data(), b->count, d_ck, b->stream);
     if (e == hipSuccess) e = copy(0);
     if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "checkpoint");
     int src = b->cur;

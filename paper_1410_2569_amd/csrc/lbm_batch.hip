@@ -325,6 +325,24 @@ __global__ __launch_bounds__(256) void k_batch_obs_final(const InstDesc* __restr
     obs_final_block(gptr(D->part), obs_rows(D->P), sh, out + 16 * blockIdx.x);
 }
 
+__global__ __launch_bounds__(kCheckpointArgs) void k_checkpoints(CheckpointArgs A, int n,
+                                                                 Checkpoints* __restrict__ table) {
+    if ((int)threadIdx.x < n) table[threadIdx.x] = A.c[threadIdx.x];
+}
+
+hipError_t launch_checkpoints(const Checkpoints* host, int count, Checkpoints* table,
+                              hipStream_t s) {
+    for (int o = 0; o < count; o += kCheckpointArgs) {
+        const int n = std::min(kCheckpointArgs, count - o);
+        CheckpointArgs A{};
+        std::copy(host + o, host + o + n, A.c);
+        hipLaunchKernelGGL(k_checkpoints, dim3(1), dim3(kCheckpointArgs), 0, s, A, n, table + o);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // ---- ensemble adjoint ---------------------------------------------------------------------------
 
 __device__ __forceinline__ void adj_tile_origin(const AdjInst* D, int t, int& x0, int& y0) {

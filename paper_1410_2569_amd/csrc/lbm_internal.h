@@ -27,6 +27,15 @@ struct Checkpoints {
     long long stride;  // doubles between consecutive states
 };
 
+// The table of a run's checkpoints, written by the stream (kCheckpointArgs entries per launch) so
+// that a checkpointed forward run neither waits for it nor keeps it from being captured.
+constexpr int kCheckpointArgs = 64;
+struct CheckpointArgs {
+    Checkpoints c[kCheckpointArgs];
+};
+hipError_t launch_checkpoints(const Checkpoints* host, int count, Checkpoints* table,
+                              hipStream_t s);
+
 // One instance of an ensemble's adjoint run (device memory): its segment of recomputed states
 // and the adjoint quantities of two consecutive reverse steps (see AdjPtrs).
 struct AdjInst {

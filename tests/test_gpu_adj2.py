@@ -37,3 +37,32 @@ def test_two_reverse_steps_bitwise_equal_single_ones(gpu, form, ratio):
             got = s.backward(n, k, w).cpu().numpy()
             assert np.isfinite(got).all() and np.abs(got).max() > 0
             assert np.array_equal(got, ref), (c[0]["nx"], n, k)
+
+
+def test_checkpointed_forward_of_an_ensemble_can_be_captured(gpu):
+    """A caller's graph capture of the checkpointed forward run (it has no host synchronisation):
+    the replay leaves the state and the gradients of a run that was launched directly."""
+    import torch
+
+    p = synth.base_params(nx=96, ny=42, wall_force="modpsi", rho_v=0.0008901265340675707,
+                          rho_l=0.445063267033785)
+    rho = synth.droplet_rho(96, 42, p["rho_l"], p["rho_v"], [(48.0, 0.5)], [12.0], seed=3)
+    gw = [synth.gw_smooth(96, -0.02, 0.02, k) for k in (3, 4)]
+    ends = []
+    for captured in (False, True):
+        s = torch.cuda.Stream()
+        b = gpu.Batch([p, p], gw, [rho, rho], tune={"tile": 1, "schedule": 2}, stream=s)
+        ws = b.adjoint_workspace(11, 4)
+        if captured:
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=s):
+                b.forward_ckpt(11, 4, ws)
+            with torch.cuda.stream(s):
+                g.replay()
+        else:
+            b.forward_ckpt(11, 4, ws)
+        b.loss()
+        ends.append([b.f(0), b.f(1)] + [x.cpu().numpy() for x in b.backward(11, 4, ws)])
+    for x, y in zip(*ends):
+        assert np.isfinite(x).all() and np.array_equal(x, y)
