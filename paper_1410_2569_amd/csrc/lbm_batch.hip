@@ -625,9 +625,14 @@ int obs_tiles(const KParams& P) {
 
 hipError_t launch_batch_obs(const InstDesc* inst, int count, int max_blocks, const double* y_wall,
                             int cur, double* out, hipStream_t s) {
-    hipLaunchKernelGGL(k_batch_obs, dim3(max_blocks, count), dim3(256), 0, s, inst, y_wall, cur);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    constexpr int kGridY = 65535;  // instances per launch: a grid's second dimension ends at 65536
+    for (int o = 0; o < count; o += kGridY) {
+        const dim3 g(max_blocks, std::min(kGridY, count - o));
+        hipLaunchKernelGGL(k_batch_obs, g, dim3(256), 0, s, inst + o, y_wall ? y_wall + o : nullptr,
+                           cur);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k_batch_obs_final, dim3(count), dim3(256), 0, s, inst, out);
     return hipGetLastError();
 }
