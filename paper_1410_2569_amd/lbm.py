@@ -187,12 +187,15 @@ def check(rc: int, ctx=None):
         raise LBMError(rc, msg)
 
 
+# A prototype of this module's own: the function objects in C.pythonapi are shared by the process.
+_bytes_of_size = C.PYFUNCTYPE(C.py_object, C.c_void_p, C.c_ssize_t)(
+    ("PyBytes_FromStringAndSize", C.pythonapi))
+
+
 def _new_bytes(n: int):
     """A bytes object of n bytes yet to be filled, and its address. Filled once, before anyone else
     holds it: no zeroed buffer and no copy of a state that may take hundreds of megabytes."""
-    make = C.pythonapi.PyBytes_FromStringAndSize
-    make.restype, make.argtypes = C.py_object, [C.c_char_p, C.c_ssize_t]
-    b = make(None, n)
+    b = _bytes_of_size(None, n)
     return b, C.cast(C.c_char_p(b), C.c_void_p)
 
 
