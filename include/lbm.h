@@ -410,6 +410,12 @@ int64_t lbm_current_step(const lbm_ctx *c);
 int lbm_fp64_probe(const double *d_a, const double *d_b, double *d_sqrt, double *d_quot, size_t n,
                    void *stream);
 
+/* Results of 8 MiB and more (densities, populations, saved states) reach host memory through pinned
+ * buffers, which the library makes as calls first need them and then keeps: at most four of 8 MiB in
+ * the process (calls beyond four at a time copy without one). This frees those that no call is
+ * using, and waits for all of the device's work meanwhile, as freeing pinned memory does. */
+int lbm_release_host_buffers(void);
+
 /* Release a context (host memory only). Waits for the work queued on its stream first, so the
  * caller may free the workspace as soon as it returns; LBM_E_HIP if that wait failed (the
  * context is released all the same). */

@@ -6,9 +6,9 @@ its thin Python binding.
 from .lbm import (ABI_VERSION, EOS, SCHEDULE, WALL, WALLS, Batch, Droplets, LBMError, Obs,  # noqa: F401
                   Params, Sim, Tune, autotune, cs_temperature, lib, make_droplets, make_params,
                   maxwell_cs,
-                  observables_of_state, piecewise_spinodals, workspace_size)
+                  observables_of_state, piecewise_spinodals, release_host_buffers, workspace_size)
 
 __all__ = ["Sim", "Batch", "Tune", "autotune", "Params", "Obs", "LBMError", "make_params",
            "Droplets", "make_droplets",
-           "maxwell_cs", "cs_temperature", "piecewise_spinodals", "workspace_size", "observables_of_state", "lib", "WALL",
-           "WALLS", "EOS", "SCHEDULE", "ABI_VERSION"]
+           "maxwell_cs", "cs_temperature", "piecewise_spinodals", "workspace_size", "observables_of_state",
+           "release_host_buffers", "lib", "WALL", "WALLS", "EOS", "SCHEDULE", "ABI_VERSION"]

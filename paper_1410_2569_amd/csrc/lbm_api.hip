@@ -102,26 +102,66 @@ void parallel_memcpy(char* dst, const char* src, size_t n) {
         if (t.joinable()) t.join();
 }
 
-// A large copy from the device into pageable host memory, through two pinned buffers of the call's
-// own: one is on its way over PCIe (57 GB/s) while threads copy the other, which also spreads the
-// page faults of a fresh host array. hipMemcpy reaches 17 GB/s into pageable memory, 10 GB/s into a
-// fresh array: 151 MB 16.1 -> 7.1 ms, 38 MB 3.6 -> 1.9, 12 MB 1.0 -> 0.65 (2 threads 9.8, 2.1, 0.76;
-// 8 threads 8.9, 2.2, 0.71). Towards the device hipMemcpy stays: its host pages are there already,
-// and creating a 1500 x 1001 lattice took 15.0-20.7 ms with staged uploads, 11.9-16.1 without.
-hipError_t staged_read(hipStream_t s, char* dst, const char* src, size_t bytes) {
-    char* buf[2] = {};
-    hipEvent_t ev[2] = {};
-    hipError_t e = hipHostMalloc((void**)&buf[0], 2 * kStageChunk, hipHostMallocDefault);
-    if (e != hipSuccess) {  // no pinned memory to be had
+// Pinned buffers of the large copies to the host, two chunks each. The process keeps what it has
+// made, because freeing pinned memory waits for every stream of the device: at most kStageBuffers
+// (32 MiB), each lent to one call at a time, whatever its context, stream or thread.
+// lbm_release_host_buffers gives them back.
+class StageBuffers {
+public:
+    char* take() {  // null: all are lent, or there is no pinned memory to be had
+        {
+            std::lock_guard<std::mutex> lock(m_);
+            if (idle_) return buf_[--idle_];
+            if (made_ == kStageBuffers) return nullptr;
+            ++made_;
+        }
+        void* p = nullptr;
+        if (hipHostMalloc(&p, 2 * kStageChunk, hipHostMallocPortable) == hipSuccess) return (char*)p;
         (void)hipGetLastError();
-        return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+        std::lock_guard<std::mutex> lock(m_);
+        --made_;
+        return nullptr;
     }
-    buf[1] = buf[0] + kStageChunk;
+    void give(char* p) {
+        std::lock_guard<std::mutex> lock(m_);
+        buf_[idle_++] = p;
+    }
+    hipError_t release() {  // those that no call holds
+        std::lock_guard<std::mutex> lock(m_);
+        hipError_t e = hipSuccess;
+        for (; idle_; --made_) {
+            const hipError_t r = hipHostFree(buf_[--idle_]);
+            if (e == hipSuccess) e = r;
+        }
+        return e;
+    }
+
+private:
+    static constexpr int kStageBuffers = 4;
+    std::mutex m_;
+    char* buf_[kStageBuffers] = {};
+    int idle_ = 0, made_ = 0;
+};
+StageBuffers g_stage;
+
+// A large copy from the device into pageable host memory, through a pinned buffer of two chunks:
+// one is on its way over PCIe (57 GB/s) while threads copy the other, which also spreads the
+// page faults of a fresh host array. Reading populations out into a fresh array, by hipMemcpy and
+// so: 604 MB 56.6 -> 22.7 ms, 151 MB 14.2 -> 5.8, 38 MB 3.6 -> 1.7, 12 MB 0.69 -> 0.35, 8.7 MB
+// 0.50 -> 0.31 (of two, four and eight threads four were best). Towards the device hipMemcpy stays:
+// its host pages are there already, and creating a 1500 x 1001 lattice took 15.0-20.7 ms with staged
+// uploads, 11.9-16.1 without.
+hipError_t staged_read(hipStream_t s, char* dst, const char* src, size_t bytes) {
+    char* const base = g_stage.take();
+    if (!base) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+    char* const buf[2] = {base, base + kStageChunk};
+    hipEvent_t ev[2] = {};
+    hipError_t e = hipSuccess;
     for (int k = 0; k < 2 && e == hipSuccess; ++k)
         e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
     const size_t n = (bytes + kStageChunk - 1) / kStageChunk;
     auto len = [&](size_t i) { return std::min(kStageChunk, bytes - i * kStageChunk); };
-    auto start = [&](size_t i) {  // chunk i into its buffer
+    auto start = [&](size_t i) {  // chunk i into its half
         hipError_t r = hipMemcpyAsync(buf[i & 1], src + i * kStageChunk, len(i),
                                       hipMemcpyDeviceToHost, s);
         return r == hipSuccess ? hipEventRecord(ev[i & 1], s) : r;
@@ -132,11 +172,15 @@ hipError_t staged_read(hipStream_t s, char* dst, const char* src, size_t bytes) 
         if (e == hipSuccess) e = hipEventSynchronize(ev[i & 1]);
         if (e == hipSuccess) parallel_memcpy(dst + i * kStageChunk, buf[i & 1], len(i));
     }
-    const hipError_t es = hipStreamSynchronize(s);
+    const hipError_t es = hipStreamSynchronize(s);  // nothing still writes the buffer
     for (int k = 0; k < 2; ++k)
         if (ev[k]) (void)hipEventDestroy(ev[k]);
-    (void)hipHostFree(buf[0]);
-    return e != hipSuccess ? e : es;
+    g_stage.give(base);
+    if (e != hipSuccess && es == hipSuccess) {  // no such copy here (events of another device)
+        (void)hipGetLastError();
+        return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost);
+    }
+    return es;
 }
 
 // Dense host array [planes][rows][nx] -> device field with rows `pitch` and planes `plane`
@@ -2057,6 +2101,11 @@ int lbm_fp64_probe(const double* d_a, const double* d_b, double* d_sqrt, double*
     const hipError_t e = lbm::launch_fp64_probe(d_a, d_b, d_sqrt, d_quot, (long long)n,
                                                 (hipStream_t)stream);
     return e == hipSuccess ? LBM_OK : create_fail(LBM_E_HIP, "fp64 probe", e);
+}
+
+int lbm_release_host_buffers(void) {
+    (void)hipGetLastError();  // report only errors of this call
+    return g_stage.release() == hipSuccess ? LBM_OK : LBM_E_HIP;
 }
 
 int lbm_destroy(lbm_ctx* c) {

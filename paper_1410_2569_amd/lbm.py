@@ -144,6 +144,7 @@ SIGNATURES = {
                                C.POINTER(C.c_double)]),
     "lbm_fp64_probe": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_size_t,
                                  C.c_void_p]),
+    "lbm_release_host_buffers": (C.c_int, []),
     "lbm_destroy": (C.c_int, [C.c_void_p]),
     "lbm_strerror": (C.c_char_p, [C.c_int]),
     "lbm_last_error": (C.c_char_p, [C.c_void_p]),
@@ -298,6 +299,12 @@ def fp64_probe(a, b, stream=None):
                                C.c_void_p(sq.data_ptr()), C.c_void_p(qt.data_ptr()), a.numel(),
                                C.c_void_p(st.cuda_stream)))
     return sq, qt
+
+
+def release_host_buffers():
+    """Free the pinned buffers that large results go through (at most 32 MiB, made again when next
+    needed). Waits for all of the device's work."""
+    check(lib().lbm_release_host_buffers())
 
 
 def workspace_size(q: Params) -> int:
