@@ -252,11 +252,11 @@ int lbm_set_gw(lbm_ctx *c, const double *gw_host);
  *   2      (default) two time steps per launch (the first step's populations stay in LDS;
  *          72 bytes per lattice update), an odd remainder step runs fused; output tile 64x8,
  *          or the wide 32x4 workgroups (schedule 39) on lattices of at most 384 such tiles.
- *          Lattices of up to about 65,000 nodes take four steps per launch where so many are asked
- *          for (tiles of 8x4 to 16x8 nodes, the populations between steps in LDS), unless an output
- *          tile was chosen (32+t). Lattices without a solid mask that fill the GPU (from about a million nodes) take three
- *          steps per launch instead, by strips that march through registers (48 bytes per lattice
- *          update), with the same exception;
+ *          Lattices of up to about 65,000 nodes take four steps per launch where so many are
+ *          asked for (tiles of 8x4 to 16x8 nodes, the populations between steps in LDS).
+ *          Lattices without a solid mask that fill the GPU (from about a million nodes) take
+ *          three, by strips that march through registers (48 bytes per lattice update). An output
+ *          tile (32+t) chooses neither; schedule 2 undoes that choice;
  *   16+t   fused with tile shape t (0..7: 64x4, 64x8, 64x16, 128x4, and the overlapped
  *          62-column tiles with 4, 6, 8, 14 rows);
  *   32+t   two steps per launch with output tile t (0..5: 64x8, 64x4, 128x4, 64x16, 32x8,

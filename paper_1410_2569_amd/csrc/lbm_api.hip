@@ -625,6 +625,19 @@ static uint64_t splitmix64_host(uint64_t z) {
     return z ^ (z >> 31);
 }
 
+// The launches of schedule 2 as a context has them at first: output tile, multi-step tile, marching.
+static void default_launches(lbm_ctx* c) {
+    const KParams& P = c->kp;
+    const lbm::MarchShape shape{P.nx, P.y_hi - P.y_lo + 1};
+    // 64 x 8 output tiles, or the wide 32 x 4 workgroups on lattices of at most 384 such tiles
+    // (about 1.5 per compute unit), which a launch runs in one round of short chains. Measured
+    // per two-step launch (one MI355X; 64x8 / 64x4 / wide 32x4): 128x64 7.24 / 6.54 / 5.55 us,
+    // 256x128 7.35 / 6.74 / 5.78, 384x192 7.76 / 8.58 / 7.98, 512x256 8.39 / 9.44 / 10.56.
+    c->tile2 = ((shape.nx + 31) / 32) * ((shape.rows + 3) / 4) <= 384 ? 7 : 0;
+    c->steps = lbm::steps_tile_of(shape.nx, shape.rows);
+    c->march = P.mask ? 0 : lbm::march_rows(&shape, 1);
+}
+
 // One of rho0_host (host density field) and drops (droplets generated on the device) is given.
 static int create_impl(const lbm_params* p, const uint8_t* solid, const double* gw_host,
                        const double* rho0_host, const lbm_droplets* drops, void* d_ws,
@@ -679,14 +692,7 @@ static int create_impl(const lbm_params* p, const uint8_t* solid, const double* 
     c->step = 0;
     c->schedule = 2;  // two steps per launch (bit-identical to single steps, fastest)
     c->tile = 1;
-    // 64 x 8 output tiles, or the wide 32 x 4 workgroups on lattices of at most 384 such tiles
-    // (about 1.5 per compute unit), which a launch runs in one round of short chains. Measured
-    // per two-step launch (one MI355X; 64x8 / 64x4 / wide 32x4): 128x64 7.24 / 6.54 / 5.55 us,
-    // 256x128 7.35 / 6.74 / 5.78, 384x192 7.76 / 8.58 / 7.98, 512x256 8.39 / 9.44 / 10.56.
-    c->tile2 = ((p->nx + 31) / 32) * ((y_hi_of(p) - y_lo_of(p) + 4) / 4) <= 384 ? 7 : 0;
-    const lbm::MarchShape shape{p->nx, y_hi_of(p) - y_lo_of(p) + 1};
-    c->steps = lbm::steps_tile_of(shape.nx, shape.rows);
-    c->march = solid ? 0 : lbm::march_rows(&shape, 1);
+    default_launches(c);
     c->adj_start = -1;
     c->adj_nsteps = 0;
     c->adj_K = 0;
@@ -775,7 +781,11 @@ int lbm_set_schedule(lbm_ctx* c, int32_t schedule) {
     // the overlapped fused tiles (16 + 4..7).
     if (c->kp.mask && schedule >= 20 && schedule < 32)
         return fail(c, LBM_E_INVAL, "a solid mask has no overlapped-tile schedule (tiles 4-7)");
-    if (schedule >= 0 && schedule <= 2) { c->schedule = schedule; return LBM_OK; }
+    if (schedule >= 0 && schedule <= 2) {
+        if (schedule == 2) default_launches(c);  // undoes the choice of an output tile
+        c->schedule = schedule;
+        return LBM_OK;
+    }
     if (schedule >= 16 && schedule < 16 + lbm::n_tiles()) {
         c->schedule = 0;
         c->tile = schedule - 16;
