@@ -575,6 +575,27 @@ static bool psi_defined(const lbm_params* p, double rho) {
     return std::isfinite(rad) && rad >= 0.0;
 }
 
+// The number of fluid nodes of an initial density field, or -1 where one of their densities is not
+// positive, finite and inside the pseudopotential's domain. A function of its own, which holds the
+// loop's values in registers: inlined into the creation of a context the loop kept some of them on
+// the stack (creating 2048 x 1024 of Eq. (15) 8.1 ms, 6.8 so; Carnahan-Starling 9.9, 8.7).
+__attribute__((noinline)) static long long fluid_densities(const lbm_params* p, const uint8_t* solid,
+                                                           const double* rho0) {
+    const lbm_params q = *p;
+    const int nx = q.nx, lo = solid ? 0 : y_lo_of(&q), hi = solid ? q.ny - 1 : y_hi_of(&q);
+    long long n = 0;
+    for (int y = lo; y <= hi; ++y) {
+        const double* rho = rho0 + (long long)y * nx;
+        const uint8_t* m = solid ? solid + (long long)y * nx : nullptr;
+        for (int x = 0; x < nx; ++x) {
+            if (m && m[x]) continue;
+            if (!finite_pos(rho[x]) || !psi_defined(&q, rho[x])) return -1;
+            ++n;
+        }
+    }
+    return n;
+}
+
 int lbm_pressure(const lbm_params* p, double rho, double* out) {
     if (!out || validate(p, nullptr) != LBM_OK) return LBM_E_INVAL;
     return host_pressure(p, rho, out) ? LBM_OK : LBM_E_INVAL;
@@ -652,15 +673,7 @@ static int create_impl(const lbm_params* p, const uint8_t* solid, const double* 
     if (p->walls && !gw_host) return LBM_E_INVAL;
     if (is_mask(p) != (solid != nullptr)) return LBM_E_INVAL;
     if (rho0_host) {
-        // every fluid density positive, finite and inside the pseudopotential's domain
-        long long nfluid = 0;
-        for (long long i = 0; i < (long long)p->nx * p->ny; ++i) {
-            const int y = (int)(i / p->nx);
-            if (solid ? solid[i] != 0 : (y < y_lo_of(p) || y > y_hi_of(p))) continue;
-            if (!finite_pos(rho0_host[i]) || !psi_defined(p, rho0_host[i])) return LBM_E_INVAL;
-            ++nfluid;
-        }
-        if (nfluid == 0) return LBM_E_INVAL;
+        if (fluid_densities(p, solid, rho0_host) <= 0) return LBM_E_INVAL;
     } else {
         // the droplet profiles lie between rho_v (1 - jitter) and rho_l (1 + jitter)
         const double lo = p->rho_v * (1.0 - drops->jitter), hi = p->rho_l * (1.0 + drops->jitter);
@@ -1479,11 +1492,7 @@ static int batch_create_impl(const lbm_params* p, int32_t count,
         b->fin.push_back((double*)(base + L.off_fin));
         for (int t = 0; t < B.ntx[i] * B.nty[i]; ++t) tile_inst[B.tile0[i] + t] = i;
         const uint8_t* solid = solid_host ? solid_host[i] : nullptr;
-        for (long long k = 0; k < (long long)p[i].nx * p[i].ny; ++k) {
-            const int y = (int)(k / p[i].nx);
-            if (solid ? solid[k] != 0 : (y < y_lo_of(&p[i]) || y > y_hi_of(&p[i]))) continue;
-            if (!finite_pos(rho0_host[i][k]) || !psi_defined(&p[i], rho0_host[i][k])) { delete b; return LBM_E_INVAL; }
-        }
+        if (fluid_densities(&p[i], solid, rho0_host[i]) < 0) { delete b; return LBM_E_INVAL; }
         const int gw_rows = solid ? p[i].ny : 2;
         if (gw_host[i]) {
             for (long long k = 0; k < (long long)gw_rows * p[i].nx; ++k)
