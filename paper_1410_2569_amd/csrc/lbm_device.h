@@ -71,13 +71,16 @@ __device__ __forceinline__ int wrapx(int x, int nx) {
 
 // Quotient, reciprocal and square root of the time step, correctly rounded wherever operands and
 // results lie well inside the range of doubles (densities, pseudopotentials and velocities do):
-// Newton's iteration on the hardware's reciprocal (square root) estimate and a last correction by
-// the exact remainder (P. Markstein, "Computation of elementary functions on the IBM RISC
-// System/6000 processor", 1990). The compiler's own division and square root make the same
-// iterations, with the same bits, between steps that scale operands out of the denormal range and
-// put special values back: 4 and 3 instructions of 11 per division and 5 of 17 per square root,
-// all on the dependent chain. A zero divisor gives NaN here where those give an infinity; the
-// node is not finite either way.
+// Newton's iteration on the hardware's reciprocal estimate (Goldschmidt's coupled one for the square
+// root) and a last correction by the exact remainder (P. Markstein, "Computation of elementary
+// functions on the IBM RISC System/6000 processor", 1990). The compiler's own division and square
+// root make the same iterations, with the same bits, between steps that scale operands out of the
+// denormal range and put special values back: 4 and 3 instructions of 11 per division and 5 of 17
+// per square root, all on the dependent chain. The observables' velocity and the reverse step use
+// the compiler's. What is different here: a zero or infinite divisor gives NaN, where the
+// compiler's gives an infinity or a zero (a node with such a density is not finite either way, and
+// is counted as such), and near the ends of the range, where a remainder is subnormal, the last bit
+// may be off.
 #ifdef __AMDGCN__
 __device__ __forceinline__ double recip(double b) {
 #pragma clang fp contract(off)

@@ -541,16 +541,19 @@ hipError_t launch_droplets(const KParams& P, const DropletArgs& D, double* rho, 
     return hipGetLastError();
 }
 
-// The device's FP64 square root and division as the step kernels compile them: sq = sqrt(a),
-// qt = a / b, element-wise.
+// The device's FP64 square root and division, element-wise: sq = sqrt(a), qt = a / b. Operands of
+// magnitudes well inside the range of doubles, as the step's are, take its root() and quot() (recip()
+// is quot() of 1, operation by operation). The rest take the compiler's, which know zeros,
+// infinities and subnormal numbers.
 __global__ __launch_bounds__(256) void k_fp64_probe(const double* __restrict__ a,
                                                     const double* __restrict__ b,
                                                     double* __restrict__ sq,
                                                     double* __restrict__ qt, long long n) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    sq[i] = root(a[i]);
-    qt[i] = quot(a[i], b[i]);
+    auto inside = [](double v) { return fabs(v) >= 0x1p-500 && fabs(v) <= 0x1p500; };
+    sq[i] = inside(a[i]) ? root(a[i]) : sqrt(a[i]);
+    qt[i] = inside(a[i]) && inside(b[i]) ? quot(a[i], b[i]) : a[i] / b[i];
 }
 
 hipError_t launch_fp64_probe(const double* a, const double* b, double* sq, double* quot,
