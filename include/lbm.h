@@ -344,7 +344,8 @@ int lbm_batch_create_masked(const lbm_params *p, int32_t count, const uint8_t *c
                             const double *const *gw_host, const double *const *rho0_host,
                             const lbm_tune *tune, void *d_ws, size_t bytes, void *hip_stream,
                             lbm_batch **out);
-/* Advance every instance by n steps (asynchronous). */
+/* Advance every instance by n steps (asynchronous). While the caller captures the stream, the
+ * launches themselves are recorded, not the graphs that the ensemble replays otherwise. */
 int lbm_batch_step(lbm_batch *b, int64_t n);
 /* Observables of every instance into out[count]; synchronises. LBM_E_HIP if a persistent run
  * was aborted by the grid-barrier time-out (workgroups not co-resident). */

@@ -1624,10 +1624,20 @@ static int capture(lbm_batch* b, hipGraphExec_t* out, const std::function<hipErr
     return LBM_OK;
 }
 
+// The caller is capturing the ensemble's stream. A graph launched into a capture is not recorded:
+// the runtime runs it at once, and the caller's replays go without its steps.
+static bool caller_captures(const lbm_batch* b) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (b->stream == nullptr) return false;  // cannot be captured
+    if (hipStreamIsCapturing(b->stream, &st) != hipSuccess) (void)hipGetLastError();
+    return st != hipStreamCaptureStatusNone;
+}
+
 int lbm_batch_step(lbm_batch* b, int64_t n) {
     if (!b || n < 0) return LBM_E_INVAL;
     if (n == 0) return LBM_OK;
     (void)hipGetLastError();
+    const bool direct = caller_captures(b);  // launches without graphs of the ensemble's own
     if (b->tune.schedule == 1) {
         // one launch of n / 2 two-step passes, and a per-step launch for an odd last step
         if (n > (int64_t)1 << 30) return batch_fail(b, LBM_E_INVAL, "too many steps in one call");
@@ -1645,14 +1655,14 @@ int lbm_batch_step(lbm_batch* b, int64_t n) {
                                            cur ^ (npairs & 1) ^ 1, nullptr, b->stream);
             return e;
         };
-        if (!b->pgraph || b->pgraph_n != n || b->pgraph_cur != cur) {
+        if (!direct && (!b->pgraph || b->pgraph_n != n || b->pgraph_cur != cur)) {
             if (b->pgraph) { (void)hipGraphExecDestroy(b->pgraph); b->pgraph = nullptr; }
             if (capture(b, &b->pgraph, persistent) == LBM_OK) {
                 b->pgraph_n = n;
                 b->pgraph_cur = cur;
             }
         }
-        hipError_t e = b->pgraph ? hipGraphLaunch(b->pgraph, b->stream) : persistent();
+        hipError_t e = b->pgraph && !direct ? hipGraphLaunch(b->pgraph, b->stream) : persistent();
         if (e != hipSuccess) return batch_fail(b, LBM_E_HIP, "persistent launch");
         b->cur ^= (npairs & 1) ^ (int)(n & 1);
         b->step += n;
@@ -1661,7 +1671,7 @@ int lbm_batch_step(lbm_batch* b, int64_t n) {
     // replay a graph of kGraphChunk steps, then launch the remainder directly (60 steps where a
     // launch makes three: either way an even number of launches)
     const int chunk = b->tune.schedule == 2 && b->nsegs ? 60 : kGraphChunk;
-    int64_t chunks = n / chunk;
+    const int64_t chunks = direct ? 0 : n / chunk;
     for (int64_t k = 0; k < chunks; ++k) {
         const int cur = b->cur;
         if (!b->graph[cur]) {
