@@ -211,9 +211,9 @@ int lbm_observables_plane(lbm_ctx *c, double x_lo, double x_hi, double y_wall, l
  *          walls = 0;
  *   stream hipStream_t of the current device (NULL = default stream); the call synchronises it;
  *   out    host record, out->step = 0.
- * The density and pseudopotential planes and the partial sums live in a fixed 24 MiB device
- * array of the library (one per GPU, held until the process ends); nothing is allocated. A
- * lattice that needs more (about 1.5 million nodes; 1024 x 1024 fits) gets LBM_E_SIZE, with the
+ * The partial sums live in a fixed 24 MiB device array of the library (one per GPU, held until
+ * the process ends); nothing is allocated. A lattice of which two planes and the partial sums are
+ * larger than that (about 1.5 million nodes; 1024 x 1024 is accepted) gets LBM_E_SIZE, with the
  * reason in lbm_last_error(NULL). Calls that overlap on one GPU (several host threads or streams)
  * share that array and race. Returns LBM_E_NONFINITE (after filling *out) if a fluid node is not
  * finite. */

@@ -981,7 +981,8 @@ int lbm_observables_of_state(const lbm_params* p, const double* d_f, const doubl
     const KParams P = kparams_of(p, L);
     const size_t plane_b = align_up((size_t)L.plane * sizeof(double), kAlign);
     const size_t part_b = align_up((size_t)lbm::obs_blocks(P) * lbm::OBS_NQ * sizeof(double), kAlign);
-    // (the size limit of the entry point, which holds two fields of the lattice as well)
+    // The limit counts two fields of the lattice beside the partial rows, though only those rows and
+    // the final sums are stored here: the sizes that are accepted stay as they were documented.
     const size_t need = 2 * plane_b + part_b + align_up(32 * sizeof(double), kAlign);
     if (need > kStaticScratchBytes) {
         g_create_err = "observables_of_state: the lattice needs " + std::to_string(need) +

@@ -492,9 +492,10 @@ __device__ __forceinline__ void node_populations(const KParams& P, const double*
     }
 }
 
-// Density and pseudopotential of node (x, y) (x < nx, y_lo <= y <= y_hi) into psi_g and, when
-// given, rho_out (fields of [ny][pitch] doubles); a solid node of a mask gets 0 in both. With
-// ghost rows (Eq. 7 applied at the wall) the solid row next to the node's row receives its psi.
+// Pseudopotential of node (x, y) (x < nx, y_lo <= y <= y_hi) into psi_g (the psi pass of the two-pass
+// schedule) and, when given, its density into rho_out (fields of [ny][pitch] doubles); a solid node
+// of a mask gets 0 in both. With ghost rows (Eq. 7 applied at the wall) the solid row next to the
+// node's row receives its psi.
 template <bool PRE = false>
 __device__ __forceinline__ void psi_node(const KParams& P, const double* __restrict__ gin,
                                          double* __restrict__ psi_g, double* __restrict__ rho_out,
@@ -590,9 +591,10 @@ __device__ __forceinline__ void obs_values(const KParams& P, const double f[9], 
 }
 
 // Observables contribution of node (x, y) (x < nx, y_lo <= y <= y_hi) to v[O_NQ] from fields of
-// [ny][pitch] doubles: rho_f, the density of every fluid node, and psi_g, psi with its ghost rows.
-// Solid nodes of a mask contribute nothing. PRE: gin holds pre-collision populations (see
-// node_populations).
+// [ny][pitch] doubles: rho_f, the density of every fluid node, and psi_g, psi with its ghost rows, as
+// psi_node writes them. Solid nodes of a mask contribute nothing. PRE: gin holds pre-collision
+// populations (see node_populations). The kernels form these values tile by tile (obs_tile); this is
+// the reference of their emulation on the CPU, bit for bit.
 template <bool PRE = false>
 __device__ __forceinline__ void obs_node(const KParams& P, const double* __restrict__ gin,
                                          const double* __restrict__ rho_f,

@@ -123,7 +123,11 @@ __global__ __launch_bounds__(steps_threads(kTileSteps, TX, TY)) void k_steps(
 }
 
 // kMarchSteps steps per launch: every wave marches one strip through one segment of h rows
-// (march_strip). Two waves per SIMD (256 registers each): three levels hold about 200.
+// (march_strip). Two waves per SIMD, 256 registers each: three levels take 237 to 241 of them, and
+// with the wet-node wall or Eq. (15) compiled in up to all, of which most such variants spill 4 to 14
+// (8 to 35 in the ensembles' kernel, which holds two viscosities' code). The spills lie in the set-up
+// and in the rows beside a wall or seam; no plain row touches scratch memory, and the variants run
+// alike: 2048 x 1024 30.6 us per step with bounce-back and Carnahan-Starling, 30.5 with both.
 template <int GEO, int EOS, int VISC>
 __global__ __launch_bounds__(64 * kMarchWaves, 2) void k_march(
     KParams P, const double* __restrict__ gin, double* __restrict__ gout,
@@ -394,9 +398,10 @@ static int strips_of(const MarchShape& m) {
 // its first full row. Measured per row: 1.75 us with one wave per SIMD, 2.9 us for two
 // (2048 x 1024: 26 segments of 40 rows, 988 waves, 96 us per launch; 52 of 20, 1976 waves, 92 us;
 // 32 of 32, 1216 waves, 116 us). The two-step tiles make 49 updates per ns on a full chip. The
-// line lies near a million nodes: 1024 x 512 takes 11.3 us per step with tiles and 14.3 marching,
-// 1400 x 700 19.2 and 16.7, 1500 x 1001 27.7 and 23.2, 2048 x 1024 39.4 and 29.6, 4096 x 4096
-// 312 and 212.
+// line lies near a million nodes: 1024 x 512 takes 10.9 us per step with tiles and 12.4 marching (14.3
+// with periodic rows), 1400 x 700 17.4-18.3 and 17.2-17.5 (18.2), 1500 x 1001 25.3 and 22.5-24.1,
+// 2048 x 1024 40.3 and 30.6, 4096 x 4096 312 and 212. With the wet-node wall and Eq. (15) the same
+// within 5%: 13.1, 17.3, 22.7, 30.5, 211.
 int march_rows(const MarchShape* m, int count) {
     constexpr int H = 2 * kMarchSteps - 1;
     double nodes = 0.0;

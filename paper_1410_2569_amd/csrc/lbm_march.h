@@ -15,13 +15,13 @@
 // hold values of no meaning after level t, which no lane that is stored ever reads.
 //
 // What bounds it: T = 3 moves 48 bytes per update where the two-step tiles move 72, and a level
-// issues about 190 vector instructions per row against 350 per node and step of the tiles (each psi
-// and each pull is made once; the halo costs 10 of 64 lanes). On 4096 x 4096 (2.4 GB) a launch takes
-// 645 us: the vector units are busy 70% of it and memory moves 2.7 GB (4.3 TB/s; a plain copy
-// reaches 5.2), where two steps of tiles took 622 us. T = 2 is bound by memory alone (600 us per
-// launch), T = 4 spills registers (256 at two waves per SIMD) and runs 2.5 times longer. The next
-// row's loads are issued one row ahead into registers; a ring of three rows in LDS filled by direct
-// loads (4 bytes a lane) freed 18 registers and was 3% slower.
+// issues 180 vector instructions per row (195 with two viscosities) against 350 per node and step of
+// the tiles (each psi and each pull is made once; the halo costs 10 of 64 lanes). On 4096 x 4096
+// (2.4 GB) a launch takes 640 us: the vector units are busy 70% of it and memory moves 2.7 GB
+// (4.3 TB/s; a plain copy reaches 5.2), where two steps of tiles took 622 us. T = 2 is bound by memory
+// alone (600 us per launch), T = 4 spills 70 registers (of 256 at two waves per SIMD) and runs 2.5
+// times longer. The next row's loads are issued one row ahead into registers; a ring of three rows in
+// LDS filled by direct loads (4 bytes a lane) freed 18 registers and was 3% slower.
 //
 // The arithmetic of every node is that of step_tile (sum9, psi_of_rho, cohesion_sum, collide), so
 // the bits are those of T single steps.

@@ -3,10 +3,10 @@
 // What bounds such a lattice is the chain of one workgroup and the gap between dependent launches
 // (about 2 us), not arithmetic: two steps per launch took 5.4-6 us however small the lattice. Here a
 // launch makes four; the tile is small (8 x 4 to 16 x 8) and its halo of 8 rings recomputed, which
-// costs 12.5 first-step updates per node of an 8 x 4 tile on compute units that would be idle. One
-// thread per node of the first region, the ring that only needs psi on waves of its own: every phase
-// of a step is one psi or one collision deep on at most 11 waves. Per step, two-step launches and
-// these: 120 x 60 2.70 -> 1.87 us (8 x 4), 128 x 64 2.85 -> 1.89, 160 x 80 2.80 -> 1.99 (8 x 8),
+// costs 10 first-step updates (12.4 of psi) per node of an 8 x 4 tile on compute units that would be
+// idle. One thread per node of the first region, the ring that only needs psi on waves of its own:
+// every phase of a step is one psi or one collision deep on at most 11 waves. Per step, two-step
+// launches and these: 120 x 60 2.70 -> 1.87 us (8 x 4), 128 x 64 2.85 -> 1.89, 160 x 80 2.80 -> 1.99 (8 x 8),
 // 256 x 128 3.00 -> 2.32 (16 x 8), 300 x 102 2.84 -> 2.37. Three steps took 2.05, 2.09, 2.08, 2.33
 // and 2.35.
 #pragma once
