@@ -17,9 +17,10 @@ CXX = os.environ.get("CXX_EMU", "/opt/rocm/llvm/bin/clang++")
 
 pytestmark = pytest.mark.skipif(not shutil.which(CXX), reason=f"{CXX} not available")
 
-# nx ny walls ghost eos wall_force
-LATTICES = ["65 12 1 1 0 2", "63 9 0 1 0 0", "66 9 2 1 1 2", "9 5 2 0 0 1", "64 8 1 0 1 1",
-            "3 4 1 1 0 0", "70 9 3 0 0 2"]
+# nx ny walls ghost eos wall_force, rows per block
+CASES = [("65 12 1 1 0 2", 8), ("65 12 1 1 0 2", 4), ("63 9 0 1 0 0", 8), ("66 9 2 1 1 2", 4),
+         ("9 5 2 0 0 1", 8), ("64 8 1 0 1 1", 4), ("3 4 1 1 0 0", 8), ("70 9 3 0 0 2", 8),
+         ("40 7 3 0 1 0", 4)]
 
 
 def _build(out, *extra):
@@ -39,14 +40,13 @@ def emulator(tmp_path_factory):
                   "-fsanitize=address,undefined", "-fno-sanitize-recover=all")
 
 
-@pytest.mark.parametrize("rows", [4, 8])
-@pytest.mark.parametrize("lattice", LATTICES)
+@pytest.mark.parametrize("lattice,rows", CASES)
 def test_tiles_equal_the_sums_of_the_nodes(emulator, lattice, rows):
     r = _run(emulator, lattice, 0, rows)
     assert r.returncode == 0 and "ok: 0 differ" in r.stdout, (r.stdout[-2000:], r.stderr[-2000:])
 
 
-@pytest.mark.parametrize("lattice,rows", [("66 9 2 1 1 2", 8), ("9 5 2 0 0 1", 4), ("63 9 0 1 0 0", 4)])
+@pytest.mark.parametrize("lattice,rows", [("40 11 2 1 1 2", 8), ("63 6 0 1 0 0", 4)])
 def test_held_populations(emulator, lattice, rows):
     r = _run(emulator, lattice, 1, rows)
     assert r.returncode == 0 and "ok: 0 differ" in r.stdout, (r.stdout[-2000:], r.stderr[-2000:])
@@ -65,5 +65,5 @@ def test_emulator_catches_planted_mistakes(tmp_path, old, new):
     hdr.write_text(src.replace(old, new).replace('#include "lbm_device.h"',
                                                  f'#include "{CSRC}/lbm_device.h"'))
     exe = _build(str(tmp_path / "mutant"), f'-DLBM_OBS_HEADER="{hdr}"', "-fsanitize=address")
-    r = _run(exe, "65 12 1 1 0 2", 0, 8)
+    r = _run(exe, "20 13 1 1 0 2", 0, 8)
     assert r.returncode != 0, r.stdout
