@@ -214,7 +214,8 @@ bool is_mask(const lbm_params* p) { return p->walls == LBM_WALLS_MASK; }
 int y_lo_of(const lbm_params* p) { return (p->walls == 1 || p->walls == 2) ? 1 : 0; }
 int y_hi_of(const lbm_params* p) { return (p->walls == 1 || p->walls == 2) ? p->ny - 2 : p->ny - 1; }
 
-Layout layout_of(const lbm_params* p) {
+// psi: with a plane for the pseudopotential, which the two-pass schedule of a lattice alone writes.
+Layout layout_of(const lbm_params* p, bool psi = true) {
     Layout L;
     L.pitch = (int)align_up((size_t)p->nx, 32);
     L.plane = (long long)p->ny * L.pitch;
@@ -222,7 +223,8 @@ Layout layout_of(const lbm_params* p) {
     size_t o = 0;
     L.off_g0 = o; o += fbytes;
     L.off_g1 = o; o += fbytes;
-    L.off_psi = o; o += align_up((size_t)L.plane * sizeof(double), kAlign);
+    L.off_psi = o;
+    if (psi) o += align_up((size_t)L.plane * sizeof(double), kAlign);
     // G_w: two wall rows, or one value per node with a solid mask (plus its link words)
     L.off_gw = o; o += align_up((size_t)(is_mask(p) ? p->ny : 2) * L.pitch * sizeof(double), kAlign);
     L.off_links = o;
@@ -1332,7 +1334,7 @@ static int spin_limit_from_env() {
 struct BatchLayout {
     size_t off_desc, off_tiles, off_bar, off_rows, off_segs, off_obs, total;
     std::vector<lbm::MarchSeg> segs;  // schedule 2 marches these strips (none: tiles)
-    std::vector<size_t> off_inst;  // per instance: g0, g1, gw, psi, part, fin
+    std::vector<size_t> off_inst;  // per instance: g0, g1, gw, part, fin
     std::vector<Layout> L;
     int ntiles;
     std::vector<int> tile0, ntx, nty;
@@ -1352,7 +1354,7 @@ bool batch_layout(const lbm_params* p, int32_t count, int tile, BatchLayout* B) 
         B->nty[i] = (yhi - ylo + TY) / TY;
         B->tile0[i] = (int)nt;
         nt += (long long)B->ntx[i] * B->nty[i];
-        B->L[i] = layout_of(&p[i]);
+        B->L[i] = layout_of(&p[i], false);
     }
     if (nt > (1LL << 30)) return false;
     B->ntiles = (int)nt;
