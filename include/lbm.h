@@ -289,7 +289,7 @@ int lbm_set_schedule(lbm_ctx *c, int32_t schedule);
  *     segment runs on a stream the context creates on first use (default priority, destroyed by
  *     lbm_destroy) while the current segment is reversed; the context stream waits for it, so
  *     all of the call's work is ordered before later work on the context stream.
- * Memory: ceil(N/K) + 2K states of 9 * ny * round_up(nx, 32) doubles, plus 26 planes.
+ * Memory: ceil(N/K) + 2(K-1) states of 9 * ny * round_up(nx, 32) doubles, plus 26 planes.
  */
 int lbm_adjoint_workspace_size(const lbm_params *p, int64_t nsteps, int32_t K, size_t *bytes);
 int lbm_forward_ckpt(lbm_ctx *c, int64_t nsteps, int32_t K, void *d_ws, size_t bytes);
@@ -367,7 +367,7 @@ int lbm_batch_record_contact_line(lbm_batch *b, int64_t n, int32_t every, const 
  * instances with two-step launches over one work-list of 64 x 4 tiles and runs each reverse step
  * of all instances as one launch over the same work-list. Every instance's gradient is bit for bit
  * the one its lattice alone gets from lbm_backward.
- *   lbm_batch_adjoint_workspace_size: device bytes for (nsteps, K): per instance ceil(N/K) + K
+ *   lbm_batch_adjoint_workspace_size: device bytes for (nsteps, K): per instance ceil(N/K) + K-1
  *     states and the adjoint buffers of lbm_adjoint_workspace_size, plus the tables;
  *   lbm_batch_forward_ckpt: d_ws caller-owned, 256-byte aligned, >= that size;
  *   lbm_batch_loss: L[count] host array (synchronises);

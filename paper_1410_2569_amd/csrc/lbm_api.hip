@@ -395,11 +395,11 @@ struct AdjLayout {
         total;
 };
 
-// Adjoint workspace: the checkpoints, the segment store (segs of them, K states each), then the
-// adjoint quantities of two consecutive reverse steps (a: 9 planes, q: 2 planes, p0, psi', r: 4
-// rows, each twice) and the G_w gradient; the adjoint part is cleared at the start of every
-// backward pass. A single lattice keeps two segment stores (one recomputed while the other is
-// reversed), an ensemble instance one.
+// Adjoint workspace: the checkpoints, the segment store (segs of them, K - 1 states each: the first
+// state of a segment is its checkpoint), then the adjoint quantities of two consecutive reverse
+// steps (a: 9 planes, q: 2 planes, p0, psi', r: 4 rows, each twice) and the G_w gradient; the
+// adjoint part is cleared at the start of every backward pass. A single lattice keeps two segment
+// stores (one recomputed while the other is reversed), an ensemble instance one.
 AdjLayout adj_layout_of(const lbm_params* p, int64_t nsteps, int32_t K, int segs) {
     AdjLayout A;
     Layout L = layout_of(p);
@@ -412,7 +412,7 @@ AdjLayout adj_layout_of(const lbm_params* p, int64_t nsteps, int32_t K, int segs
     tmp.y_lo = p->walls ? 1 : 0; tmp.y_hi = p->walls ? p->ny - 2 : p->ny - 1;
     size_t o = 0;
     A.off_ck = o; o += (size_t)A.nck * A.fbytes;
-    A.off_seg = o; o += (size_t)segs * K * A.fbytes;
+    A.off_seg = o; o += (size_t)segs * (K - 1) * A.fbytes;
     A.off_a = o; o += 2 * A.fbytes;
     A.off_q = o; o += 4 * A.pbytes;
     A.off_p0 = o; o += 2 * A.pbytes;
@@ -1217,7 +1217,7 @@ int lbm_backward(lbm_ctx* c, int64_t nsteps, int32_t K, void* d_adj, size_t byte
     // state i of segment j: its checkpoint, or the i-th recomputed state
     auto seg = [&](int64_t j, int64_t i) {
         if (i == 0) return (double*)(w + A.off_ck + (size_t)j * A.fbytes);
-        return (double*)(w + A.off_seg + ((size_t)(j & 1) * K + (size_t)i) * A.fbytes);
+        return (double*)(w + A.off_seg + ((size_t)(j & 1) * (K - 1) + (size_t)(i - 1)) * A.fbytes);
     };
     auto seg_len = [&](int64_t j) { return std::min<int64_t>(K, nsteps - j * K); };
     auto recompute = [&](int64_t j) -> hipError_t {

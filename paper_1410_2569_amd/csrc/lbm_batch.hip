@@ -353,7 +353,8 @@ __device__ __forceinline__ void adj_tile_origin(const AdjInst* D, int t, int& x0
 
 // State i of segment j: the checkpoint itself, or the i-th recomputed state.
 __device__ __forceinline__ double* seg_state(const AdjInst* D, int i, int j) {
-    return i ? gptr(D->seg) + (long long)i * D->fstride : gptr(D->ck) + (long long)j * D->fstride;
+    return i ? gptr(D->seg) + (long long)(i - 1) * D->fstride
+             : gptr(D->ck) + (long long)j * D->fstride;
 }
 
 // Segment states i -> i+1, i+2 of every instance (two steps per launch, the first written too),
